@@ -70,10 +70,11 @@ struct qlsd_code_s {
     int min_rw;
     // host copies of the CSR row pointers and the CSC layout, for launch planning
     std::vector<int32_t> h_row_ptr, h_col_ptr, h_col_edge;
-    // message strides already chosen for (slots, LDS budget): decoders of one code (serving
-    // lanes) reuse them instead of re-running the model
+    // message strides already chosen for (slots, LDS budget, threads): decoders of one code
+    // (serving lanes) reuse them instead of re-running the model
+    struct StrideChoice { int S; size_t budget; int threads, se; };
     std::mutex stride_mu;
-    std::vector<std::pair<std::pair<int, size_t>, int>> strides;
+    std::vector<StrideChoice> strides;
 };
 
 struct qlsd_decoder_s {
@@ -90,6 +91,7 @@ struct qlsd_decoder_s {
     float *d_llr;        // max_batch x n (LLRs handed from BP to LSD)
     int bp_slots, bp_grid;
     int bp_se;           // message stride per slot (bp_msg_stride)
+    int bp_threads;      // threads per workgroup
     bool bp_graph;       // one workgroup per shot (large graphs) instead of S slots per workgroup
     int lsd_W, lsd_grid, lsd_wave_bytes, lsd_keys_in_lds, lsd_graph_in_lds;
     bool lsd_cb;         // cluster-batched column insertion (W = 4; qlsd_decoder_set_lsd_schedule)
@@ -316,17 +318,24 @@ void qlsd_code_destroy(qlsd_code c) {
 }
 
 // The slot kernel's message stride for S slots within budget bytes of LDS per workgroup.
-static int bp_stride_for(qlsd_code c, int S, size_t budget) {
+static int bp_stride_for(qlsd_code c, int S, size_t budget, int threads) {
     std::lock_guard<std::mutex> lk(c->stride_mu);
     for (const auto &e : c->strides)
-        if (e.first.first == S && e.first.second == budget) return e.second;
-    const int se = bp_msg_stride(c->g, c->h_row_ptr.data(), c->h_col_ptr.data(), c->h_col_edge.data(), S, budget);
+        if (e.S == S && e.budget == budget && e.threads == threads) return e.se;
+    const int se = bp_msg_stride(c->g, c->h_row_ptr.data(), c->h_col_ptr.data(), c->h_col_edge.data(), S, budget, threads);
     try {
-        c->strides.push_back({{S, budget}, se});
+        c->strides.push_back({S, budget, threads, se});
     } catch (...) {
     }
     return se;
 }
+
+// Threads of a slot-BP workgroup when wg of them share a CU: 16 wavefronts per CU in every shape (a
+// CU's one or two workgroups of larger graphs leave most of its issue slots empty at 256 threads).
+// BP 30 per launch, one workgroup of 256 / 512 / 1024 threads per CU: 432 x 900, 2,048 shots 0.485 /
+// 0.268 / 0.186 ms; 192 x 400, 8,192 shots 0.69 / 0.38 / 0.27; 768 x 1600, 2,048 shots 0.75 / 0.42 /
+// 0.29.  Two workgroups of 512 with half the slots each: 0.23, 0.27 and 0.39.
+static int bp_threads_for(int wg) { return wg >= 4 ? kBpThreads : wg >= 2 ? 2 * kBpThreads : kBpMaxThreads; }
 
 qlsd_status qlsd_decoder_create(qlsd_code code, const qlsd_params *params, const double *priors,
                                 int32_t max_batch, qlsd_decoder *out) {
@@ -385,11 +394,13 @@ qlsd_status qlsd_decoder_create(qlsd_code code, const qlsd_params *params, const
         d->bp_slots = S;
         d->bp_grid = std::max(1, wg_per_cu) * d->num_cus;
         const int tier = std::max(1, wg_per_cu);
-        d->bp_se = bp_stride_for(code, S, kBpLdsBudget * (4 / tier) - (tier == 1 ? 1024 : 0));
+        d->bp_threads = bp_threads_for(tier);
+        d->bp_se = bp_stride_for(code, S, kBpLdsBudget * (4 / tier) - (tier == 1 ? 1024 : 0), d->bp_threads);
     } else if (bp_graph_lds_bytes(g) <= kLdsPerCu - 1024) {
         // one workgroup per shot with the shot's messages in LDS
         d->bp_graph = true;
         d->bp_slots = 1;
+        d->bp_threads = kBpGraphThreads;
         d->bp_grid = d->num_cus;
     } else {
         delete d;
@@ -498,6 +509,15 @@ static Ws decoder_ws(qlsd_decoder d) {
     return Ws{d->d_ctl, d->d_flag, d->d_list, d->d_llr, d->d_ovf_list, d->d_ovf2_list, d->d_wide_ws, d->wide_grid};
 }
 
+// Slots per workgroup of a call of B shots: no more than spread the batch over every compute unit
+// (a small batch then puts few shots on each of many units instead of filling a few).  Beyond one
+// workgroup per unit fuller workgroups win: their slots share one pass of slot management and
+// barriers ([[144,12,12]] p = 0.01, 10,007 shots: 715 workgroups of 14 slots decode in 0.236 ms,
+// 1001 of 10 in 0.249; 500 shots: 250 of 2 in 0.255 ms, 36 of 14 in 0.270).
+static int bp_slots_used(qlsd_decoder d, int B) {
+    return std::max(1, std::min(d->bp_slots, (B + d->num_cus - 1) / d->num_cus));
+}
+
 static BpArgs bp_args(qlsd_decoder d, const Ws &w, const uint8_t *syn, int B) {
     BpArgs a;
     memset(&a, 0, sizeof(a));
@@ -508,7 +528,8 @@ static BpArgs bp_args(qlsd_decoder d, const Ws &w, const uint8_t *syn, int B) {
     a.max_iter = d->params.max_iter;
     a.alpha = d->params.ms_scaling;
     a.early_exit = (d->params.flags & QLSD_FLAG_NO_EARLY_EXIT) ? 0 : 1;
-    a.S = d->bp_slots;
+    a.threads = d->bp_threads;
+    a.S = bp_slots_used(d, B);
     a.SE = d->bp_se;
     a.next_shot = w.ctl + kCtlQueue;
     return a;
@@ -521,12 +542,12 @@ static int fuse_waves(qlsd_decoder d) {
     if (d->bp_graph || d->net || (d->params.flags & (QLSD_FLAG_SEPARATE_LSD | QLSD_FLAG_OSD0_POST))) return 0;
     if (d->lsd_W > 2 || d->params.lsd_order > 0 || !d->lsd_keys_in_lds || d->bp_grid > 4 * d->num_cus) return 0;
     const size_t avail = bp_lds_bytes(d->code->g, d->bp_slots, d->bp_se) - bp_tables_bytes(d->code->g);
-    return (int)std::min<size_t>(4, avail / (size_t)d->lsd_wave_bytes);
+    return (int)std::min<size_t>(d->bp_threads / 64, avail / (size_t)d->lsd_wave_bytes);
 }
 
 static int bp_grid(qlsd_decoder d, int B) {
-    const int need = (B + d->bp_slots - 1) / d->bp_slots;
-    return std::max(1, std::min(d->bp_grid, need));
+    const int S = bp_slots_used(d, B);
+    return std::max(1, std::min(d->bp_grid, (B + S - 1) / S));
 }
 
 static hipError_t run_bp(qlsd_decoder d, const BpArgs &a, int B, hipStream_t s) {
@@ -650,7 +671,7 @@ static qlsd_status decode_with(qlsd_decoder d, const Ws &w, const uint8_t *syndr
         f.bp_done = w.ctl + kCtlBpDone;
         f.lsd_done = w.ctl + kCtlLsdDone;
         f.lsd_waves = fw;
-        f.lsd_bytes = (int)bp_lds_bytes(d->code->g, d->bp_slots, d->bp_se);
+        f.lsd_bytes = (int)(bp_tables_bytes(d->code->g) + (size_t)fw * d->lsd_wave_bytes);
         if (timing) HIP_OK(hipEventRecord(d->ev[0], s));
         HIP_OK(launch_bp_fused(a, f, d->lsd_W, bp_grid(d, B), s));
         if (timing) HIP_OK(hipEventRecord(d->ev[1], s));
@@ -936,7 +957,7 @@ qlsd_status qlsd_decoder_tune(qlsd_decoder d, const uint8_t *syndromes, int32_t 
     };
     // BP with shot slots: the largest slot count that fits each workgroups-per-CU tier
     if (!d->bp_graph) {
-        int best_S = d->bp_slots, best_grid = d->bp_grid, best_se = d->bp_se;
+        int best_S = d->bp_slots, best_grid = d->bp_grid, best_se = d->bp_se, best_threads = d->bp_threads;
         float best = 1e30f;
         for (int wg : {1, 2, 3, 4, 5, 6, 8}) {
             const size_t budget = kLdsPerCu / wg - 512;
@@ -945,18 +966,26 @@ qlsd_status qlsd_decoder_tune(qlsd_decoder d, const uint8_t *syndromes, int32_t 
             if (S < 4) continue;
             d->bp_slots = S;
             d->bp_grid = wg * d->num_cus;
-            d->bp_se = bp_stride_for(d->code, S, budget);
+            d->bp_threads = bp_threads_for(wg);
+            d->bp_se = bp_stride_for(d->code, S, budget, d->bp_threads);
             const bool whole = d->net == nullptr;
             const float ms = whole ? timeit(decode_run) : timeit(bp_run);
             snprintf(line, sizeof(line), "%s slots %d x %d workgroups/CU: %.4f ms\n",
                      whole ? (fuse_waves(d) > 0 ? "decode (BP + LSD one kernel)," : "decode (BP, LSD),") : "bp",
                      S, wg, ms);
             rep += line;
-            if (ms > 0.f && ms < best) { best = ms; best_S = S; best_grid = d->bp_grid; best_se = d->bp_se; }
+            if (ms > 0.f && ms < best) {
+                best = ms;
+                best_S = S;
+                best_grid = d->bp_grid;
+                best_se = d->bp_se;
+                best_threads = d->bp_threads;
+            }
         }
         d->bp_slots = best_S;
         d->bp_grid = best_grid;
         d->bp_se = best_se;
+        d->bp_threads = best_threads;
         snprintf(line, sizeof(line), "bp chosen: slots %d, grid %d\n", best_S, best_grid);
         rep += line;
     }

@@ -320,8 +320,8 @@ __device__ __noinline__ int2 fuse_step(int *list, int *next_item, int *bp_done, 
 // code has more checks than the 64 W local rows, and a shot whose clusters outgrow them is listed
 // for the overflow kernels (compiled in only where it can happen: it costs registers).  At most 128
 // VGPRs (4 wavefronts per SIMD), so that four BP workgroups fit on a CU.
-template <int MAXRW, int MAXCW, bool REG, int LSDW, bool OVF = false>
-__global__ __launch_bounds__(kBpThreads) __attribute__((amdgpu_waves_per_eu(4)))
+template <int MAXRW, int MAXCW, bool REG, int LSDW, bool OVF, int NTMAX>
+__global__ __launch_bounds__(NTMAX) __attribute__((amdgpu_waves_per_eu(4)))
 void bp_lds_kernel(BpArgs args, FuseArgs f) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int t = threadIdx.x, NT = blockDim.x;
@@ -545,7 +545,7 @@ void bp_lds_kernel(BpArgs args, FuseArgs f) {
         const int ldb = L.ctl[6], ldc = L.ctl[7], ldbuf = L.ctl[8];
         const bool pending = L.ctl[5] != 0;
         // this thread's active slot for the fault phase of the iteration: t = r0 * A + a with
-        // r0 < Rs = NT div A (the division by reciprocal is exact for t < 256, A <= 128); the
+        // r0 < Rs = NT div A (the division by reciprocal is exact for t < 1024, A <= 128); the
         // NT mod A threads past Rs * A serve no slot
         int r0 = 1 << 30, Rs = NT;
         SlotView V;
@@ -890,11 +890,11 @@ int bp_min_stride(const DevGraph &g) { return odd_stride(g.nnz); }
 // bank.  Lane t of a phase serves slot t mod S of check (or fault) t div S, so the lanes of a
 // wavefront read edge u of a few consecutive checks (faults) in every slot, at slot * SE + edge.
 static long long bp_bank_cycles(const int32_t *row_ptr, const int32_t *col_ptr, const int32_t *col_edge, int m,
-                                int n, int max_rw, int max_cw, int S, int SE) {
+                                int n, int max_rw, int max_cw, int S, int SE, int threads) {
     long long cyc = 0;
     int bank[32];
     auto pass = [&](int items, int first_thread, int max_w, auto addr) {
-        const int NT = kBpThreads - first_thread;  // threads of the phase
+        const int NT = threads - first_thread;     // threads of the phase
         const int R = NT / S;                      // items per step
         for (int it = 0; it < items; it += R)
             for (int w0 = 0; w0 < NT; w0 += 64)
@@ -929,25 +929,30 @@ static long long bp_bank_cycles(const int32_t *row_ptr, const int32_t *col_ptr, 
 // check and fault phases, the chosen 437 models 1.0 and 1.5, and BP ran 6 % faster; the stride a
 // 64-bank model prefers ran slower than 437, which is why the model counts 32 banks.
 int bp_msg_stride(const DevGraph &g, const int32_t *row_ptr, const int32_t *col_ptr, const int32_t *col_edge, int S,
-                  size_t budget) {
+                  size_t budget, int threads) {
     int best = bp_min_stride(g);
     if (S < 1) return best;
     long long best_cyc = -1;
     for (int SE = g.nnz; SE < g.nnz + 64; SE++) {
         if (bp_lds_bytes(g, S, SE) > budget) break;
-        const long long c = bp_bank_cycles(row_ptr, col_ptr, col_edge, g.m, g.n, g.max_rw, g.max_cw, S, SE);
+        const long long c = bp_bank_cycles(row_ptr, col_ptr, col_edge, g.m, g.n, g.max_rw, g.max_cw, S, SE, threads);
         if (best_cyc < 0 || c < best_cyc) { best_cyc = c; best = SE; }
     }
     return best;
 }
 
-template <int RW, int CW, bool REG, int LSDW, bool OVF>
-static hipError_t launch_bp_t(const BpArgs &a, const FuseArgs &f, int grid, size_t lds, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute((const void *)bp_lds_kernel<RW, CW, REG, LSDW, OVF>,
+template <int RW, int CW, bool REG, int LSDW, bool OVF, int NTMAX>
+static hipError_t launch_bp_nt(const BpArgs &a, const FuseArgs &f, int grid, size_t lds, hipStream_t st) {
+    hipError_t e = hipFuncSetAttribute((const void *)bp_lds_kernel<RW, CW, REG, LSDW, OVF, NTMAX>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bp_lds_kernel<RW, CW, REG, LSDW, OVF>), dim3(grid), dim3(kBpThreads), lds, st, a, f);
+    hipLaunchKernelGGL((bp_lds_kernel<RW, CW, REG, LSDW, OVF, NTMAX>), dim3(grid), dim3(a.threads), lds, st, a, f);
     return hipGetLastError();
+}
+template <int RW, int CW, bool REG, int LSDW, bool OVF>
+static hipError_t launch_bp_t(const BpArgs &a, const FuseArgs &f, int grid, size_t lds, hipStream_t st) {
+    return a.threads <= kBpThreads ? launch_bp_nt<RW, CW, REG, LSDW, OVF, kBpThreads>(a, f, grid, lds, st)
+                                   : launch_bp_nt<RW, CW, REG, LSDW, OVF, kBpMaxThreads>(a, f, grid, lds, st);
 }
 
 // Large graphs, fault-major message order.  The messages of fault j sit contiguously at its CSC

@@ -10,6 +10,9 @@
 
 namespace qlsd {
 
+constexpr int kBpThreads = 256;      // slot BP: four workgroups per CU
+constexpr int kBpMaxThreads = 1024;  // slot BP: one workgroup per CU
+
 // Device copy of H: CSR (checks -> faults) and CSC (faults -> checks); edge id = CSR position.
 struct DevGraph {
     int m, n, nnz;
@@ -37,6 +40,7 @@ struct BpArgs {
     int max_iter;
     float alpha;
     int early_exit;
+    int threads;               // threads per workgroup (a multiple of 64, at most kBpMaxThreads)
     int S;                     // shot slots per workgroup
     int SE;                    // message stride per slot (floats, >= nnz; bp_msg_stride)
     int *next_shot;            // queue head (zeroed before launch)
@@ -98,7 +102,7 @@ size_t bp_lds_bytes(const DevGraph &g, int S, int SE);
 // picks for S slots within budget bytes (host copies of the CSR row pointers and the CSC layout)
 int bp_min_stride(const DevGraph &g);
 int bp_msg_stride(const DevGraph &g, const int32_t *row_ptr, const int32_t *col_ptr, const int32_t *col_edge, int S,
-                  size_t budget);
+                  size_t budget, int threads = kBpThreads);
 size_t bp_graph_lds_bytes(const DevGraph &g);
 // Builds the large-graph kernel's message layout on the host (see qlsd_bp.hip); returns the
 // LDS words it spans, or -1 when the kernel's limits rule it out.
@@ -184,7 +188,6 @@ hipError_t net_refine_listed(struct qlsd_net_s *net, const float *lam, const uin
                              const int *list, const int *list_count, int max_count, unsigned char *ws,
                              hipStream_t st);
 
-constexpr int kBpThreads = 256;
 constexpr int kBpGraphThreads = 1024;
 constexpr int kLsdThreads = 256;   // 4 wavefronts, each decodes its own shots
 constexpr int kMaxRowWeight = 32;  // BP register arrays

@@ -1,0 +1,81 @@
+"""Workgroup shapes of the slot BP kernel: 256 threads with four workgroups per compute unit, 1024
+threads with one, and batches smaller than the grid's slots, which spread over the compute units
+with fewer slots per workgroup.  BP is the same function of a shot in every shape, so posteriors of
+a shot do not depend on its batch; they are checked against the float64 oracle, and the decode
+whose BP and LSD share one kernel of 1024 threads against the two-kernel path, byte for byte."""
+import numpy as np
+import pytest
+
+import _r24
+from paper_2406_18655_amd import binding
+from paper_2406_18655_amd.workloads import CheckMatrix, bivariate_bicycle, random_34_hgp, sample
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _random_code(m=96, n=640, cw=3, p=0.01, seed=4):
+    """m <= 128 checks of weight 20: too many edges for four workgroups per compute unit, few
+    enough checks for BP and LSD in one kernel."""
+    rng = np.random.default_rng(seed)
+    H = np.zeros((m, n), dtype=np.uint8)
+    load = np.zeros(m, dtype=int)
+    for j in range(n):
+        rows = np.lexsort((rng.random(m), load))[:cw]
+        H[rows, j] = 1
+        load[rows] += 1
+    return CheckMatrix(name="random_96x640", H=H, priors=np.full(n, p))
+
+
+CODES = {"bb144": lambda: bivariate_bicycle(p=0.05), "hgp16": lambda: random_34_hgp(16, p=0.03),
+         "random96": _random_code}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("which", list(CODES))
+def test_bp_does_not_depend_on_the_batch(oracle_mod, which):
+    code = CODES[which]()
+    full = 6000
+    print(f"case bp_shapes {which}", flush=True)
+    e, S = sample(code, full, seed=31)
+    bc = binding.Code.from_dense(code.H)
+    dec = binding.Decoder(bc, code.priors, full, max_iter=30)
+    s = torch.from_numpy(S).cuda()
+    L, hard, info = dec.bp(s)
+    for B in (1, 2, 255, 256, 257, 1025, 3001):
+        print(f"  batch {B}", flush=True)
+        l, h, i = dec.bp(s[:B])
+        assert torch.equal(l.view(torch.int32), L[:B].view(torch.int32)) and torch.equal(h, hard[:B])
+        assert torch.equal(i, info[:B])
+    inf = binding.parse_info(info)
+    L32, h32 = L[:64].cpu().numpy(), hard[:64].cpu().numpy()
+    oc = oracle_mod.Code.from_dense(code.H)
+    lam = oracle_mod.llr_from_priors(code.priors)
+    for b in range(64):
+        _r24.check_shot(oracle_mod, oc, lam, S[b], 30, L32[b], inf["status"][b] & 1, inf["bp_iters"][b], hard32=h32[b])
+
+
+@pytest.mark.parametrize("B", [1, 300, 5000])
+def test_one_kernel_of_wide_workgroups_equals_two(B):
+    code = _random_code(p=0.02)
+    print(f"case bp_shapes fused {B}", flush=True)
+    e, S = sample(code, B, seed=32)
+    bc = binding.Code.from_dense(code.H)
+    s = torch.from_numpy(S).cuda()
+    one = binding.Decoder(bc, code.priors, B, max_iter=20)
+    two = binding.Decoder(bc, code.priors, B, max_iter=20, flags=binding.FLAG_SEPARATE_LSD)
+    c1, i1 = one.decode(s, want_info=True)
+    c2, i2 = two.decode(s, want_info=True)
+    torch.cuda.synchronize()
+    assert torch.equal(c1, c2) and torch.equal(i1, i2)
+    if B >= 300:
+        assert (binding.parse_info(i1)["status"] & binding.ST_LSD_RUN).any()
