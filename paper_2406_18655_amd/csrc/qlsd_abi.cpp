@@ -289,6 +289,11 @@ qlsd_status qlsd_code_create(int32_t m, int32_t n, int64_t nnz, const int32_t *r
     c->g.fault_msg = msg_words > 0 ? c->d_fault_msg : nullptr;
     c->g.row_msg = msg_words > 0 ? c->d_row_msg : nullptr;
     c->g.msg_words = std::max(msg_words, 0);
+    c->g.deep_cw = 0;
+    if (n > kBpGraphThreads) {
+        const int j = fault_order[kBpGraphThreads];
+        c->g.deep_cw = col_ptr[j + 1] - col_ptr[j];
+    }
     c->min_rw = min_rw;
     try {
         c->h_row_ptr.assign(row_ptr, row_ptr + m + 1);

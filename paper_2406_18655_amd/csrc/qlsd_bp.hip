@@ -4,7 +4,8 @@
 //   check -> fault : r_{i->j} = (-1)^{s_i} * alpha * prod_{j' != j} sgn(q_{j'->i}) * min_{j' != j} |q_{j'->i}|
 //   fault -> check : q_{j->i} = lambda_j + sum_{i' != i} r_{i'->j},  L_j = lambda_j + sum_i r_{i->j}
 //   hard decision  : e_j = [L_j < 0]; a shot has converged once H e = s (tested after every iteration).
-// Magnitudes of q and L are clamped to 2^64 so that 100 iterations cannot overflow float32.
+// Magnitudes of q and L are clamped to 2^64 so that 100 iterations cannot overflow float32 (the q's
+// clamp is taken on the check's minima, which gives the same messages: 2 instead of one per edge).
 //
 // Design (MI355X): a workgroup owns S shot "slots" whose messages live entirely in LDS, slot after
 // slot at a stride the host picks with a model of the LDS banks (bp_msg_stride), so the lanes that
@@ -147,10 +148,10 @@ struct FaultItem {
             // The suffix sum starts at the last edge rather than at +0: the same values, since a
             // prefix sum is -0 only if the prior is, and log((1-p)/p) never rounds to -0.
             float suf = r[CW - 1];
-            V.msg[eid[CW - 1]] = clampf(pre[CW - 1]);
+            V.msg[eid[CW - 1]] = pre[CW - 1];
 #pragma unroll
             for (int u = CW - 2; u >= 0; u--) {
-                V.msg[eid[u]] = clampf(pre[u] + suf);
+                V.msg[eid[u]] = pre[u] + suf;
                 suf += r[u];
             }
         } else {
@@ -158,12 +159,12 @@ struct FaultItem {
 #pragma unroll
             for (int u = CW - 1; u >= 0; u--) {
                 if (u < cw) {
-                    V.msg[eid[u]] = clampf(pre[u] + suf);
+                    V.msg[eid[u]] = pre[u] + suf;
                     suf += r[u];
                 }
             }
         }
-        const float Lt = clampf(pre[CW]);  // padding entries add exact zeros
+        const float Lt = pre[CW];  // padding entries add exact zeros; clamped when it is written out
         V.Lv[j] = Lt;
         if (count_parity && Lt < 0.f) {
 #pragma unroll
@@ -207,7 +208,9 @@ struct CheckItem {
             mn2 = __builtin_amdgcn_fmed3f(mn1, mn2, a);
             mn1 = __builtin_amdgcn_fmed3f(mn1, a, ninf);
         }
-        float m1 = alpha * mn1, m2 = alpha * mn2;
+        // the clamp of |q| to 2^64 taken on the minima: the smallest of the clamped is the clamped
+        // smallest, and where it binds both products are alpha 2^64, so the choice below is the same
+        float m1 = alpha * __builtin_amdgcn_fmed3f(mn1, kClamp, ninf), m2 = alpha * __builtin_amdgcn_fmed3f(mn2, kClamp, ninf);
         // keep the two products (otherwise the multiply is repeated after every select)
         asm volatile("" : "+v"(m1), "+v"(m2));
 #pragma unroll
@@ -615,7 +618,7 @@ void bp_lds_kernel(BpArgs args, FuseArgs f) {
             const size_t row = (size_t)shot * n;
             const bool write_corr = args.corr && (LSDW == 0 || conv);  // fused: LSD writes the rest
             for (int j = t - 64; j < n; j += NT - 64) {
-                const float Lj = L.Lv[k * L.SN + j];
+                const float Lj = clampf(L.Lv[k * L.SN + j]);
                 if (write_corr) args.corr[row + j] = Lj < 0.f ? 1 : 0;
                 if (args.llr_out) args.llr_out[row + j] = Lj;
                 if (!conv && args.llr_lsd) {
@@ -955,222 +958,251 @@ static hipError_t launch_bp_t(const BpArgs &a, const FuseArgs &f, int grid, size
                                    : launch_bp_nt<RW, CW, REG, LSDW, OVF, kBpMaxThreads>(a, f, grid, lds, st);
 }
 
-// Large graphs, fault-major message order.  The messages of fault j sit contiguously at its CSC
-// positions col_ptr[j] .. col_ptr[j+1]; each thread keeps the graph structure it touches in
-// registers for the kernel's lifetime -- for each of its FPT faults the index, CSC start, degree
-// and prior, and for its check row (needs m <= NT) the CSC positions of the row's edges -- so the
-// iteration loop reads no graph tables (only the row indices of faults whose hard decision is 1,
-// for the parity words).  Thread t takes the faults at positions t + k*NT of the code's fault
-// order and the check at position t of its check order (both by decreasing weight), so almost
-// every wavefront's 64 faults, or checks, have one weight: such a wavefront runs its loops over
-// the messages to that weight with scalar branches only, the few mixed ones with a per-lane test
-// on each message.  Same arithmetic, in the same order, as bp_graph_kernel; which thread computes
-// a fault or a check changes no result.
-template <int MAXRW, int MAXCW, int FPT>
-__global__ __launch_bounds__(kBpGraphThreads) void bp_graph2_kernel(BpArgs args) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int t = threadIdx.x, NT = blockDim.x;
-    const int m = args.g.m, n = args.g.n, MW = args.g.msg_words;
-    const int PW = (m + 31) / 32;
-    float *msg = (float *)smem;  // the layout of bp_graph2_layout: fault entry u at its word + 64 u
-    float *Lv = msg + MW;
-    uint32_t *synw = (uint32_t *)(Lv + n);
-    uint32_t *parw = synw + PW;
-    int *ctl = (int *)(parw + PW);
-    const int32_t *row_idx = args.g.row_idx;
-    const float alpha = args.alpha;
-    const int T = args.max_iter;
-    const int lane = t & 63, wave = t >> 6;
+// Message words of bp_graph3_kernel (the layout's, or one per fault: at a shot's end they hold its
+// posteriors) and the byte offset of its check states, after the messages and one word of +inf.
+__host__ __device__ inline int bp_graph3_words(const DevGraph &g) { return g.msg_words > g.n ? g.msg_words : g.n; }
+__host__ __device__ inline size_t bp_graph3_state_offset(const DevGraph &g) {
+    return align16(sizeof(float) * ((size_t)bp_graph3_words(g) + 1));
+}
 
-    // fault record: LDS word of its first message (15 bits) | fault (14 bits) << 15 | degree (3 bits)
-    // << 29; a record of degree 0 is no fault
-    uint32_t fmeta[FPT];
-    float flam[FPT];
+// Large graphs, check messages kept as check states.  The messages min-sum sends from one check take
+// two magnitudes and one sign product, so the check phase only writes a state per check -- the smallest
+// |q| and the second smallest, each with the sign product in its sign bit -- and the fault phase forms
+// r = +-alpha * (|q| == smallest ? second : smallest) per edge from the state and the q it sent.
+// (Rewriting every message in both phases, as this kernel's predecessor did, the check phase read
+// each message twice and wrote it, 12 VALU instructions an edge against 3.)  No graph table is read
+// in the iteration loop: each thread keeps the structure it touches in registers, and the parity
+// words of the hard decision are addressed by the same packed check positions as the states.  The
+// posteriors stay in registers until the shot ends, and a shot's syndrome test runs beside the next
+// check phase (two barriers an iteration).
+//
+// Layout: messages as bp_graph2_layout places them (entry u of the fault in lane l of group g at word
+// base_g + 64 u + l); thread t takes the faults at positions t + k NT of the code's fault order and
+// the check at position t of its check order (both by decreasing weight), whose state is entry t.  A
+// group of 64 faults runs the code compiled for its largest degree (at most 7 for the first 1024
+// faults, LIM for the rest: the packed offsets are registers); a lighter fault's missing edges point
+// at state m, which is zero and adds +-0, and a lighter check's at a word of +inf, so no loop tests
+// a lane's own weight.  Same values as bp_graph_kernel: the same products, and sums in the same order
+// (the first fault phase, with no incoming messages, is q = lambda, below 2^64); minima and sign products
+// do not depend on the order a check visits its edges.
+//
+// BP 100 of 16,384 shots of the 936 x 8800 detector error model: 10.31 -> 5.51 ms (8.7 ms where LIM is 7
+// and the row's addresses spill), 37 shots at BP 30: 0.240 -> 0.130 ms.  Bound by VALU issue (busy 0.75
+// of CU cycles, LDS 0.60 with bank conflicts 0.19, before the clamps left the edges: about 446 VALU
+// instructions per wavefront and iteration then, 400 now).  A fault order that halved the modelled
+// conflicts of the state reads changed nothing.
+template <int MAXRW, int FPT, int LIM>
+__global__ __launch_bounds__(kBpGraphThreads) void bp_graph3_kernel(BpArgs args) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NT = kBpGraphThreads;
+    constexpr int CMAX = 7;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int m = args.g.m, n = args.g.n, MW = bp_graph3_words(args.g);
+    float *msg = (float *)smem;                                         // MW words, then one of +inf
+    float2 *state = (float2 *)(smem + bp_graph3_state_offset(args.g));  // m + 1
+    uint32_t *parw = (uint32_t *)(state + m + 1);                       // NT / 32 + 1
+    int *ctl = (int *)(parw + NT / 32 + 1);  // [0] next shot, [1] last iteration found unsatisfied
+
+    // check positions, then this thread's faults and check
+    uint16_t *pos = (uint16_t *)smem;
+    if (t < m) pos[args.g.check_order[t]] = (uint16_t)t;
+    __syncthreads();
+    int grp[FPT];                       // wave-uniform: the group's first message word | largest degree << 16
+    float lam[FPT];
+    uint32_t chk[FPT][(CMAX + 1) / 2];  // byte offsets of the states of the fault's checks, two u16
 #pragma unroll
     for (int k = 0; k < FPT; k++) {
+        const int lim = k == 0 ? CMAX : LIM;
         const int p = t + k * NT;
-        uint32_t v = 0;
-        float l = 0.f;
+        int cw = 0, c0 = 0, b = 0;
+        lam[k] = 0.f;
         if (p < n) {
             const int j = args.g.fault_order[p];
-            v = (uint32_t)args.g.fault_msg[j] | ((uint32_t)j << 15) |
-                ((uint32_t)(args.g.col_ptr[j + 1] - args.g.col_ptr[j]) << 29);
-            l = args.lam[j];
+            c0 = args.g.col_ptr[j];
+            cw = args.g.col_ptr[j + 1] - c0;
+            b = args.g.fault_msg[j] - lane;
+            lam[k] = args.lam[j];
         }
-        fmeta[k] = v;
-        flam[k] = l;
-    }
-    uint32_t rpos2[MAXRW / 2];  // LDS words of the row's messages in visiting order, two u16 per word
-    const int ci = t < m ? args.g.check_order[t] : m;  // this thread's check (m: none)
-    int rw = 0;
-    if (ci < m) {
-        const int e0 = args.g.row_ptr[ci];
-        rw = args.g.row_ptr[ci + 1] - e0;
+        grp[k] = __builtin_amdgcn_readfirstlane(b | (cw << 16));  // decreasing weight: lane 0 has the largest
 #pragma unroll
-        for (int u = 0; u < MAXRW; u += 2) {
-            const uint32_t lo = u < rw ? (uint32_t)args.g.row_msg[e0 + u] : 0u;
-            const uint32_t hi = u + 1 < rw ? (uint32_t)args.g.row_msg[e0 + u + 1] : 0u;
-            rpos2[u / 2] = lo | (hi << 16);
+        for (int u = 0; u < lim; u += 2) {
+            const uint32_t lo = u < cw ? pos[args.g.row_idx[c0 + u]] : m;
+            const uint32_t hi = u + 1 < cw ? pos[args.g.row_idx[c0 + u + 1]] : m;
+            chk[k][u / 2] = (lo << 3) | (hi << 19);
         }
     }
+    uint32_t qa[MAXRW];  // byte addresses of the row's messages in visiting order
+    const int ci = t < m ? args.g.check_order[t] : 0;
+    int rw = 0;
+    {
+        const int e0 = args.g.row_ptr[ci];
+        if (t < m) rw = args.g.row_ptr[ci + 1] - e0;
+#pragma unroll
+        for (int u = 0; u < MAXRW; u++) qa[u] = 4u * (u < rw ? (uint32_t)args.g.row_msg[e0 + u] : (uint32_t)MW);
+    }
+    const int rwmax = __builtin_amdgcn_readfirstlane(rw);  // decreasing weight: lane 0 has the largest
+    __syncthreads();  // the position table is dead
+    if (t == 0) {
+        msg[MW] = INFINITY;
+        state[m] = make_float2(0.f, 0.f);
+    }
+    for (int w = t; w < NT / 32 + 1; w += NT) parw[w] = 0u;
+    const float alpha = args.alpha;
+    const int T = args.max_iter;
+    // infinities the compiler cannot see through keep the minima single med3 instructions
+    float pinf = INFINITY, ninf = -INFINITY;
+    asm volatile("" : "+v"(pinf), "+v"(ninf));
 
-    for (;;) {
-        if (t == 0) ctl[0] = atomicAdd(args.next_shot, 1);
-        __syncthreads();
-        const int shot = ctl[0];
-        if (shot >= args.B) break;
-        const uint8_t *syn = args.syn + (size_t)shot * m;
-        for (int i0 = wave * 64; i0 < m; i0 += NT) {
-            const int i = i0 + lane;
-            const uint64_t bits = __ballot(i < m && (syn[i] & 1));
-            if (lane == 0) {
-                synw[i0 >> 5] = (uint32_t)bits;
-                if ((i0 >> 5) + 1 < PW) synw[(i0 >> 5) + 1] = (uint32_t)(bits >> 32);
-            }
+    int shot = blockIdx.x;
+    while (shot < args.B) {
+        int nxt = 0;
+        if (t == 0) nxt = gridDim.x + atomicAdd(args.next_shot, 1);  // in flight while this shot runs
+        const uint32_t sb = t < m ? args.syn[(size_t)shot * m + ci] & 1u : 0u;
+        float L[FPT];
+        // (opaque copies here and in the outputs: what depends only on the thread would otherwise be
+        // kept in registers across the whole kernel)
+        int ls = lane;
+        asm volatile("" : "+v"(ls));
+#pragma unroll
+        for (int k = 0; k < FPT; k++) {
+            float q0 = lam[k];
+            asm volatile("" : "+v"(q0));
+            L[k] = q0;  // what a fault without checks keeps
+            for (int u = 0; u < grp[k] >> 16; u++) msg[(grp[k] & 0xffff) + ls + 64 * u] = q0;
         }
-        for (int w = t; w < PW; w += NT) parw[w] = 0u;
-        for (int e = t; e < MW; e += NT) msg[e] = 0.f;  // r = 0: the first fault phase sets q = lambda
+        if (t == 0) ctl[1] = 0;
         __syncthreads();
         int it = 0;
         bool conv = false;
         for (;;) {
-            // fault phase
-            // one fault's update; CWU: the wavefront's common degree (a run-time but wave-uniform
-            // bound, scalar branches only) or, for a mixed wavefront, the lane's own degree
-            auto fault_update = [&](int k, auto Uni) -> float {
-                constexpr bool UNI = decltype(Uni)::value;
-                const int c0 = (int)(fmeta[k] & 0x7fffu), cw = (int)(fmeta[k] >> 29);
-                const int cwb = UNI ? __builtin_amdgcn_readfirstlane(cw) : cw;
-                float r[MAXCW];
+            // syndrome test of the hard decision after iteration it (this wavefront's 64 checks: two
+            // parity words, which it clears)
+            if (it > 0) {
+                const uint32_t w = parw[t >> 5];
+                const bool bad = t < m && ((w >> (t & 31)) & 1u) != sb;
+                if (__ballot(bad) != 0ull && lane == 0) ctl[1] = it;
+                if ((lane & 31) == 0) parw[t >> 5] = 0u;
+            }
+            // check phase
+            if (it < T && rwmax > 0) {
+                uint32_t sg = sb << 31;
+                float mn1 = pinf, mn2 = pinf;
 #pragma unroll
-                for (int u = 0; u < MAXCW; u++) r[u] = u < cwb ? msg[c0 + 64 * u] : 0.f;
-                float pre[MAXCW + 1];
-                pre[0] = flam[k];
+                for (int u0 = 0; u0 < MAXRW; u0 += 8) {
+                    if (u0 < rwmax) {
+                        float q[8];
 #pragma unroll
-                for (int u = 0; u < MAXCW; u++) pre[u + 1] = pre[u] + r[u];
-                float suf = 0.f;
+                        for (int u = 0; u < 8; u++) q[u] = *(const float *)(smem + qa[u0 + u]);
 #pragma unroll
-                for (int u = MAXCW - 1; u >= 0; u--) {
-                    if (u < cwb) {
-                        msg[c0 + 64 * u] = clampf(pre[u] + suf);
-                        suf += r[u];
-                    }
-                }
-                return clampf(pre[MAXCW]);
-            };
-            // a uniform wavefront's degree as a compile-time constant: no branches in the loops
-            auto fault_fixed = [&](int k, auto Dc) -> float {
-                constexpr int D = decltype(Dc)::value;
-                const int c0 = (int)(fmeta[k] & 0x7fffu);
-                float r[D];
-#pragma unroll
-                for (int u = 0; u < D; u++) r[u] = msg[c0 + 64 * u];
-                float pre[D + 1];
-                pre[0] = flam[k];
-#pragma unroll
-                for (int u = 0; u < D; u++) pre[u + 1] = pre[u] + r[u];
-                float suf = 0.f;
-#pragma unroll
-                for (int u = D - 1; u >= 0; u--) {
-                    msg[c0 + 64 * u] = clampf(pre[u] + suf);
-                    suf += r[u];
-                }
-                // the remaining MAXCW - D terms of the general form add +0 to pre[D]
-                float last = pre[D];
-#pragma unroll
-                for (int u = D; u < MAXCW; u++) last = last + 0.f;
-                return clampf(last);
-            };
-#pragma unroll
-            for (int k = 0; k < FPT; k++) {
-                const int cw = (int)(fmeta[k] >> 29);
-                const int cwk = __builtin_amdgcn_readfirstlane(cw);
-                const bool uni = __ballot(cw != cwk) == 0;
-                float Lt = 0.f;
-                if (uni) {
-                    switch (cwk) {
-                        case 0: break;
-                        case 1: Lt = fault_fixed(k, std::integral_constant<int, 1>{}); break;
-                        case 2: Lt = fault_fixed(k, std::integral_constant<int, 2>{}); break;
-                        case 3: Lt = fault_fixed(k, std::integral_constant<int, 3>{}); break;
-                        case 4: Lt = fault_fixed(k, std::integral_constant<int, 4>{}); break;
-                        default: Lt = fault_update(k, std::true_type{}); break;
-                    }
-                } else if (cw > 0) {
-                    Lt = fault_update(k, std::false_type{});
-                }
-                if (cw > 0) {
-                    const int j = (int)((fmeta[k] >> 15) & 0x3fffu);
-                    Lv[j] = Lt;
-                    if (Lt < 0.f) {
-                        const int cs = args.g.col_ptr[j];  // the fault's CSC entries
-                        for (int u = 0; u < cw; u++) {
-                            const int i = row_idx[cs + u];
-                            atomicXor(parw + (i >> 5), 1u << (i & 31));
+                        for (int u = 0; u < 8; u++) {
+                            sg ^= __float_as_uint(q[u]);
+                            const float a = fabsf(q[u]);
+                            mn2 = __builtin_amdgcn_fmed3f(mn1, mn2, a);
+                            mn1 = __builtin_amdgcn_fmed3f(mn1, a, ninf);
                         }
                     }
                 }
+                // the clamp of |q| to 2^64 taken on the minima (the smallest of the clamped is the clamped
+                // smallest; where it binds both minima are 2^64 and either choice below is the same)
+                mn1 = __builtin_amdgcn_fmed3f(mn1, kClamp, ninf);
+                mn2 = __builtin_amdgcn_fmed3f(mn2, kClamp, ninf);
+                sg &= 0x80000000u;
+                if (t < m) state[t] = make_float2(__uint_as_float(__float_as_uint(mn1) | sg), __uint_as_float(__float_as_uint(mn2) | sg));
             }
             __syncthreads();
-            // syndrome test of the hard decision after iteration it (it >= 1)
-            if (wave == 0) {
-                bool ok = true;
-                for (int w = lane; w < PW; w += 64) {
-                    ok &= parw[w] == synw[w];
-                    parw[w] = 0u;
-                }
-                const bool all = __ballot(!ok) == 0;
-                if (lane == 0) ctl[1] = all ? 1 : 0;
+            if (it > 0) {
+                conv = ctl[1] != it;
+                if ((args.early_exit && conv) || it >= T) break;
             }
-            __syncthreads();
-            const bool sat = ctl[1] != 0;
-            conv = it >= 1 && sat;
-            if ((args.early_exit && conv) || it >= T) break;
             it++;
-            // check phase: thread t owns check t; two passes over the row's messages (minima and
-            // sign, then the updates) instead of holding them in registers
-            auto check_update = [&](auto Uni) {
-                constexpr bool UNI = decltype(Uni)::value;
-                const int rwb = UNI ? __builtin_amdgcn_readfirstlane(rw) : rw;
-                const uint32_t sb = (synw[ci >> 5] >> (ci & 31)) & 1u;
-                uint32_t sg = sb << 31;
-                float mn1 = INFINITY, mn2 = INFINITY;
+            // fault phase.  The packed offsets are made opaque here: their unpacked forms are loop
+            // invariant, and hoisted they would not fit the 128 registers of a 1024-thread workgroup.
+            int lo = lane;
+            asm volatile("" : "+v"(lo));
 #pragma unroll
-                for (int u = 0; u < MAXRW; u++) {
-                    if (u < rwb) {
-                        const float q = msg[(rpos2[u / 2] >> (16 * (u & 1))) & 0xffffu];
-                        sg ^= __float_as_uint(q);
-                        const float a = fabsf(q);
-                        mn2 = __builtin_amdgcn_fmed3f(mn1, mn2, a);
-                        mn1 = fminf(mn1, a);
+            for (int k = 0; k < FPT; k++)
+#pragma unroll
+                for (int u = 0; u < (k == 0 ? CMAX : LIM); u += 2) asm volatile("" : "+v"(chk[k][u / 2]));
+            auto fault = [&](auto Dc, int k) -> float {
+#pragma clang fp contract(off)  // the products round before the sums, as in bp_graph_kernel
+                constexpr int D = decltype(Dc)::value;
+                float *mk = msg + (grp[k] & 0xffff) + lo;
+                float q[D], r[D];
+                float2 s[D];
+#pragma unroll
+                for (int u = 0; u < D; u++) {
+                    q[u] = mk[64 * u];
+                    s[u] = *(const float2 *)((const unsigned char *)state + ((chk[k][u / 2] >> (16 * (u & 1))) & 0xffffu));
+                }
+#pragma unroll
+                for (int u = 0; u < D; u++) {
+                    // +-alpha times the chosen minimum, whose sign bit holds the check's sign product
+                    const float x = fabsf(q[u]) == fabsf(s[u].x) ? s[u].y : s[u].x;
+                    r[u] = x * copysignf(alpha, q[u]);
+                }
+                float pre[D + 1];
+                pre[0] = lam[k];
+#pragma unroll
+                for (int u = 0; u < D; u++) pre[u + 1] = pre[u] + r[u];
+                // the suffix sum starts at the last edge rather than at +0 (the same values: a prefix
+                // sum is -0 only if the prior is, and log((1-p)/p) never rounds to -0)
+                float suf = r[D - 1];
+                mk[64 * (D - 1)] = pre[D - 1];
+#pragma unroll
+                for (int u = D - 2; u >= 0; u--) {
+                    mk[64 * u] = pre[u] + suf;
+                    suf += r[u];
+                }
+                const float Lt = pre[D];
+                if (Lt < 0.f) {
+#pragma unroll
+                    for (int u = 0; u < D; u++) {
+                        // a missing edge flips the bit of position m, which no check reads
+                        uint32_t c = chk[k][u / 2];
+                        asm volatile("" : "+v"(c));  // unpacked here only, on the rare lanes
+                        const uint32_t b = ((c >> (16 * (u & 1))) & 0xffffu) >> 3;
+                        atomicXor(parw + (b >> 5), 1u << (b & 31));
                     }
                 }
-                const float m1 = alpha * mn1, m2 = alpha * mn2;
-#pragma unroll
-                for (int u = 0; u < MAXRW; u++) {
-                    if (u < rwb) {
-                        const int p = (rpos2[u / 2] >> (16 * (u & 1))) & 0xffffu;
-                        const float q = msg[p];
-                        const float mag = (fabsf(q) == mn1) ? m2 : m1;
-                        const uint32_t sgn = (sg ^ __float_as_uint(q)) & 0x80000000u;
-                        msg[p] = __uint_as_float(__float_as_uint(mag) | sgn);
-                    }
-                }
+                return Lt;
             };
-            {
-                const bool uni = __ballot(rw != __builtin_amdgcn_readfirstlane(rw)) == 0;
-                if (uni) {
-                    if (__builtin_amdgcn_readfirstlane(rw) > 0) check_update(std::true_type{});
-                } else if (rw > 0) {
-                    check_update(std::false_type{});
+#pragma unroll
+            for (int k = 0; k < FPT; k++) {
+                switch (grp[k] >> 16) {
+                    case 0: break;
+                    case 1: L[k] = fault(std::integral_constant<int, 1>{}, k); break;
+                    case 2: L[k] = fault(std::integral_constant<int, 2>{}, k); break;
+                    case 3: L[k] = fault(std::integral_constant<int, 3>{}, k); break;
+                    case 4: L[k] = fault(std::integral_constant<int, 4>{}, k); break;
+                    default:
+                        if constexpr (LIM > 4) {
+                            if (grp[k] >> 16 == 5) L[k] = fault(std::integral_constant<int, 5>{}, k);
+                            else if (grp[k] >> 16 == 6) L[k] = fault(std::integral_constant<int, 6>{}, k);
+                            else L[k] = fault(std::integral_constant<int, CMAX>{}, k);
+                        } else if (k == 0) {
+                            if (grp[k] >> 16 == 5) L[k] = fault(std::integral_constant<int, 5>{}, 0);
+                            else if (grp[k] >> 16 == 6) L[k] = fault(std::integral_constant<int, 6>{}, 0);
+                            else L[k] = fault(std::integral_constant<int, CMAX>{}, 0);
+                        }
+                        break;
                 }
             }
             __syncthreads();
         }
-        // outputs
+        // outputs: the messages are dead (every check phase that reads them ended before the last
+        // barrier), so the posteriors go through their words for coalesced rows
+        int to = t;
+        asm volatile("" : "+v"(to));
+#pragma unroll
+        for (int k = 0; k < FPT; k++) {
+            const int p = to + k * NT;
+            if (p < n) msg[args.g.fault_order[p]] = clampf(L[k]);
+        }
+        if (t == 0) ctl[0] = nxt;
+        __syncthreads();
         const size_t row = (size_t)shot * n;
-        for (int j = t; j < n; j += NT) {
-            const float Lj = Lv[j];
+        for (int j = to; j < n; j += NT) {
+            const float Lj = msg[j];
             if (args.corr) args.corr[row + j] = Lj < 0.f ? 1 : 0;
             if (args.llr_out) args.llr_out[row + j] = Lj;
             if (!conv && args.llr_lsd) args.llr_lsd[row + j] = Lj;
@@ -1188,19 +1220,27 @@ __global__ __launch_bounds__(kBpGraphThreads) void bp_graph2_kernel(BpArgs args)
             }
             if (args.lsd_flag) args.lsd_flag[shot] = conv ? 0 : 1;
         }
+        shot = ctl[0];
         __syncthreads();
     }
 }
 
 size_t bp_graph_lds_bytes(const DevGraph &g) {
-    // messages (the CSC order of bp_graph_kernel, or the padded layout of bp_graph2_kernel),
-    // posteriors, syndrome and parity words, control words
+    // messages (the CSC order of bp_graph_kernel, or the padded layout), posteriors, syndrome and
+    // parity words, control words
     const size_t PW = ((size_t)g.m + 31) / 32;
     const size_t words = std::max<size_t>((size_t)g.nnz, (size_t)std::max(g.msg_words, 0));
     return align16(sizeof(float) * (words + g.n) + sizeof(uint32_t) * 2 * PW + sizeof(int) * 4);
 }
 
-// Message layout of bp_graph2_kernel, chosen so that both phases' LDS accesses spread over the
+// messages and the +inf word, m + 1 check states, parity words, control words: below 140 KB, since the
+// layout spans less than 32,768 words
+static size_t bp_graph3_lds_bytes(const DevGraph &g) {
+    return align16(bp_graph3_state_offset(g) + sizeof(float2) * ((size_t)g.m + 1) +
+                   sizeof(uint32_t) * (kBpGraphThreads / 32 + 1) + sizeof(int) * 2);
+}
+
+// Message layout of bp_graph3_kernel, chosen so that both phases' LDS accesses spread over the
 // banks (gfx950 serves a wavefront's 32-bit LDS accesses as two halves of 32 lanes over 32 banks
 // of 4 bytes).  Fault phase: lane l of the wavefront that takes positions 64 g .. 64 g + 63 of the
 // weight order reads entry u of its fault at word base_g + 64 u + l, so the 32 lanes of a half
@@ -1318,25 +1358,28 @@ static hipError_t launch_bp_graph_t(const BpArgs &a, int grid, size_t lds, hipSt
     return hipGetLastError();
 }
 
-template <int RW, int CW, int FPT>
-static hipError_t launch_bp_graph2_t(const BpArgs &a, int grid, size_t lds, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute((const void *)bp_graph2_kernel<RW, CW, FPT>,
+template <int RW, int FPT, int LIM>
+static hipError_t launch_bp_graph3_t(const BpArgs &a, int grid, hipStream_t st) {
+    const size_t lds = bp_graph3_lds_bytes(a.g);
+    hipError_t e = hipFuncSetAttribute((const void *)bp_graph3_kernel<RW, FPT, LIM>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bp_graph2_kernel<RW, CW, FPT>), dim3(grid), dim3(kBpGraphThreads), lds, st, a);
+    hipLaunchKernelGGL((bp_graph3_kernel<RW, FPT, LIM>), dim3(grid), dim3(kBpGraphThreads), lds, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_bp_graph(const BpArgs &a, int grid, hipStream_t st) {
     const size_t lds = bp_graph_lds_bytes(a.g);
-    // register-resident structure: checks <= threads, row weight <= 32, column weight <= 8, u16
-    // CSC positions, at most 9 faults per thread (the 936 x 8800 detector error model)
+    // register-resident structure: checks <= threads, row weight <= 32, column weight <= 7, at most
+    // 9 faults per thread (the 936 x 8800 detector error model), a layout of less than 2^15 words
     const DevGraph &g = a.g;
-    // the packed fault record needs nnz < 2^15, n < 2^14, column weight <= 7
-    if (g.m <= kBpGraphThreads && g.max_rw <= 32 && g.max_cw <= 7 && g.nnz < 32768 && g.n <= 9 * kBpGraphThreads &&
-        g.n < 16384 && g.fault_order && g.check_order && g.fault_msg && g.row_msg && g.msg_words > 0 &&
-        g.msg_words < 32768)
-        return launch_bp_graph2_t<32, 8, 9>(a, grid, lds, st);
+    if (g.m <= kBpGraphThreads && g.max_rw <= 32 && g.max_cw <= 7 && g.n <= 9 * kBpGraphThreads && g.fault_order &&
+        g.check_order && g.fault_msg && g.row_msg && g.msg_words > 0 && g.msg_words < 32768) {
+        // offsets of up to four checks for the faults past the first 1024 fit in registers; of up to
+        // seven they do not quite (the row's addresses are then re-read from scratch: 8.7 against
+        // 5.5 ms on the detector error model, still ahead of the 10.3 ms of messages rewritten in LDS)
+        return g.deep_cw <= 4 ? launch_bp_graph3_t<32, 9, 4>(a, grid, st) : launch_bp_graph3_t<32, 9, 7>(a, grid, st);
+    }
     if (a.g.max_rw <= 8 && a.g.max_cw <= 4) return launch_bp_graph_t<8, 4>(a, grid, lds, st);
     if (a.g.max_rw <= 16 && a.g.max_cw <= 8) return launch_bp_graph_t<16, 8>(a, grid, lds, st);
     return launch_bp_graph_t<kMaxRowWeight, kMaxColWeight>(a, grid, lds, st);

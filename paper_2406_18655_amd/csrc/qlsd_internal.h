@@ -29,6 +29,7 @@ struct DevGraph {
     const uint16_t *row_msg;            // nnz: per check, in CSR slots, the LDS words of its messages
                                         // in the order the check phase visits them
     int msg_words;                      // LDS words the layout spans
+    int deep_cw;                        // column weight at position kBpGraphThreads of fault_order (0: none)
 };
 
 // Arguments of the BP kernel (messages resident in LDS, persistent slots).

@@ -79,3 +79,49 @@ def test_one_kernel_of_wide_workgroups_equals_two(B):
     assert torch.equal(c1, c2) and torch.equal(i1, i2)
     if B >= 300:
         assert (binding.parse_info(i1)["status"] & binding.ST_LSD_RUN).any()
+
+
+def _weighted_graph(m, n, probs, seed):
+    """Columns of weight w with probability probs[w], rows of weight 2 to 32."""
+    rng = np.random.default_rng(seed)
+    H = np.zeros((m, n), dtype=np.uint8)
+    load = np.zeros(m, dtype=np.int64)
+    w = rng.choice(len(probs), size=n, p=probs)
+    for j in range(n):
+        k = min(int(w[j]), int((load < 32).sum()))
+        rows = rng.choice(np.nonzero(load < 32)[0], size=k, replace=False)
+        H[rows, j] = 1
+        load[rows] += 1
+    for i in np.nonzero(load < 2)[0]:
+        cols = np.nonzero((H.sum(0) < len(probs) - 1) & (H[i] == 0))[0]
+        H[i, rng.choice(cols, size=2 - int(load[i]), replace=False)] = 1
+    return H, rng.uniform(0.001, 0.05, size=n)
+
+
+# one workgroup per shot: every instantiation of the fault phase (columns past the first 1024 of
+# weight up to 7, or up to 4 with heavier ones first), columns of weight 0, 1024 checks, 9216 faults
+LARGE = {"heavy": (700, 3300, [0, 0, .05, .1, .15, .2, .25, .25]),
+         "edges": (1024, 9216, [.05, .2, .45, .2, .06, .02, .01, .01]),
+         "light": (900, 8000, [0, .1, .9])}
+
+
+@pytest.mark.parametrize("which", list(LARGE))
+@pytest.mark.parametrize("flags", [0, binding.FLAG_NO_EARLY_EXIT])
+def test_large_graph_posteriors(oracle_mod, which, flags):
+    m, n, probs = LARGE[which]
+    H, priors = _weighted_graph(m, n, probs, seed=len(which))
+    assert H.sum(1).min() >= 2 and H.sum(1).max() <= 32
+    rng = np.random.default_rng(3)
+    e = (rng.random((5, n)) < priors / 4).astype(np.uint8)
+    S = ((e.astype(np.int64) @ H.T.astype(np.int64)) & 1).astype(np.uint8)
+    T = 15
+    print(f"case bp_shapes large {which} {flags}", flush=True)
+    dec = binding.Decoder(binding.Code.from_dense(H), priors, 5, max_iter=T, flags=flags)
+    llr, hard, info = dec.bp(torch.from_numpy(S).cuda())
+    torch.cuda.synchronize()
+    L32, h32, inf = llr.cpu().numpy(), hard.cpu().numpy(), binding.parse_info(info)
+    oc = oracle_mod.Code.from_dense(H)
+    lam = oracle_mod.llr_from_priors(priors)
+    for b in range(5):
+        _r24.check_shot(oracle_mod, oc, lam, S[b], T, L32[b], inf["status"][b] & 1, inf["bp_iters"][b],
+                        early_exit=flags == 0, hard32=h32[b])
