@@ -1,9 +1,8 @@
 // Learned reliability refinement between BP and LSD (include/qlsd_net.h): a 3-layer
 // message-passing network over the Tanner graph, hidden width 32.  Dense products run on
-// bf16 MFMA (v_mfma_f32_16x16x16bf16_1k, float32 accumulate); neighbour means in float32.
-// One workgroup (4 wavefronts) per shot at a time; node features of the shot stay in LDS.
-// Training keeps the weight-gradient tiles of the nine 32x32 matrices in registers across all
-// shots a workgroup processes and adds them to the global gradient once per workgroup.
+// bf16 MFMA with float32 accumulation; neighbour means in float32.  Training: one workgroup of 16
+// wavefronts per shot at a time, node features in LDS, and the gradient of every parameter in
+// registers across all shots a workgroup processes, added to the global gradient once per workgroup.
 #include <math.h>
 #include <string.h>
 
@@ -21,7 +20,6 @@ namespace {
 constexpr int HID = 32;
 constexpr int NL = 3;
 constexpr int NPAR = QLSD_NET_PARAMS;
-constexpr int kNetThreads = 256;
 // parameter offsets (floats)
 constexpr int P_W0 = 0, P_B0 = 64, P_LAYER = 96, P_LSTRIDE = 3136;
 constexpr int P_A = 0, P_a = 1024, P_B = 1056, P_C = 2080, P_b = 3104;
@@ -41,7 +39,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     const float2v v = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
 }
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+
 
 __host__ __device__ inline int pad16(int x) { return (x + 15) & ~15; }
 __host__ __device__ inline size_t al16(size_t x) { return (x + 15) & ~size_t(15); }
@@ -54,13 +52,12 @@ struct NetArgs {
     const float *llr;       // B x n
     const uint8_t *err;     // B x n (training)
     float *llr_out;         // B x n (inference)
-    const int *list;        // shots to process (nullable: 0..count-1)
+    const int *list;        // inference: shots to process (nullable: 0..count-1)
     const int *list_count;  // device count when list != nullptr
     int count;
     float *grad;            // NPAR (training, accumulated)
     float *loss;            // 1 (training, accumulated)
     float inv_total;        // 1 / (shots * n) (training)
-    int train;
     unsigned char *act;     // activation workspace, one slice per workgroup (nullptr: in LDS)
     size_t act_stride;      // bytes per slice
     const uint32_t *nbc;    // large-graph inference: [MP][max_rw] byte offsets of fault rows (padded)
@@ -71,26 +68,11 @@ struct NetArgs {
     const int32_t *tdeg;    // [NP/16] largest fault degree of each 16-row tile
 };
 
-struct NetLds {
-    int n, m, E, NP, MP;
-    uint16_t *wbf;               // 9 x 1024 bf16: [layer][A,B,C][out][in]
-    float *sv;                   // small vectors
-    float *svg;                  // their gradient accumulators (training)
-    uint16_t *rp, *ci, *cp, *ri;
-    float *lam, *Lsh;            // n, n
-    uint16_t *Hb[NL + 1];        // NP x 32
-    uint16_t *Cb[NL + 1];        // MP x 32 (index 1..3)
-    uint16_t *AGG;               // max(NP,MP) x 32
-    uint16_t *DUV;               // max(NP,MP) x 32 (training)
-    float *DH, *DT, *DC;         // NP x 32, max x 32, MP x 32 (training)
-    float *misc;                 // [0] loss accumulator
-};
-
-// Per-workgroup storage.  The shared part (bf16 weights, small vectors and their gradient
-// accumulators, u16 CSR/CSC tables, the loss accumulator) always sits in LDS.  The activation
-// part (the shot's BP posteriors, features of every layer, aggregation and backward buffers)
-// sits in LDS after it when both fit, else in a workgroup-private slice of a device workspace
-// (large graphs such as the 936 x 8800 detector error model); the kernels address both the same way.
+// Training: per-workgroup storage.  The shared part (bf16 weights, small vectors, u16 CSR/CSC tables)
+// always sits in LDS; net_shared_layout is also the measure of the graphs a net accepts.  The
+// activation part (the shot's inputs, features of every layer, aggregation and backward buffers) sits
+// in LDS after it when both fit, else in a workgroup-private slice of a device workspace (large
+// graphs such as the 936 x 8800 detector error model).
 __host__ __device__ inline size_t net_shared_layout(int n, int m, int E, bool train, size_t *o) {
     size_t off = 0;
     o[0] = off; off += al16(sizeof(uint16_t) * 9 * 1024);
@@ -100,343 +82,510 @@ __host__ __device__ inline size_t net_shared_layout(int n, int m, int E, bool tr
     o[4] = off; off += al16(sizeof(float) * 4);
     return off;
 }
-__host__ __device__ inline size_t net_act_layout(int n, int m, bool train, size_t *o) {
+// Inputs (posteriors, tanh, scaled priors, true errors, reciprocal degrees of faults; syndrome signs,
+// reciprocal degrees of checks), features of every layer, the aggregation (one row per feature) and the
+// masked gradient (bf16), the gradients of
+// the fault features and of the products (float).
+__host__ __device__ inline size_t net_act_layout(int n, int m, size_t *o) {
     const int NP = pad16(n), MP = pad16(m), XP = NP > MP ? NP : MP;
     size_t off = 0;
-    o[0] = off; off += al16(sizeof(float) * (size_t)n);
+    o[0] = off; off += al16(sizeof(float) * (5 * (size_t)n + 2 * (size_t)m));
     o[1] = off; off += al16(sizeof(uint16_t) * ((NL + 1) * (size_t)NP * HID + NL * (size_t)MP * HID));
-    o[2] = off; off += al16(sizeof(uint16_t) * (size_t)XP * HID);
-    o[3] = off; off += train ? al16(sizeof(uint16_t) * (size_t)XP * HID) : 0;
-    o[4] = off; off += train ? al16(sizeof(float) * ((size_t)NP + XP + MP) * HID) : 0;
+    o[2] = off; off += al16(sizeof(uint16_t) * (size_t)(XP + 4) * HID);
+    o[3] = off; off += al16(sizeof(uint16_t) * (size_t)XP * HID);
+    o[4] = off; off += al16(sizeof(float) * ((size_t)NP + XP) * HID);
     return off;
 }
-
-__device__ NetLds carve_net(unsigned char *base, unsigned char *act, int n, int m, int E, bool train,
-                            const float *lam) {
-    size_t o[5], a5[5];
-    net_shared_layout(n, m, E, train, o);
-    net_act_layout(n, m, train, a5);
-    NetLds L;
-    L.n = n; L.m = m; L.E = E; L.NP = pad16(n); L.MP = pad16(m);
-    const int XP = L.NP > L.MP ? L.NP : L.MP;
-    L.wbf = (uint16_t *)(base + o[0]);
-    L.sv = (float *)(base + o[1]);
-    L.svg = (float *)(base + o[2]);
-    L.rp = (uint16_t *)(base + o[3]);
-    L.ci = L.rp + (m + 1);
-    L.cp = L.ci + E;
-    L.ri = L.cp + (n + 1);
-    L.misc = (float *)(base + o[4]);
-    L.lam = (float *)lam;
-    L.Lsh = (float *)(act + a5[0]);
-    uint16_t *a = (uint16_t *)(act + a5[1]);
-    for (int l = 0; l <= NL; l++) { L.Hb[l] = a; a += (size_t)L.NP * HID; }
-    L.Cb[0] = nullptr;
-    for (int l = 1; l <= NL; l++) { L.Cb[l] = a; a += (size_t)L.MP * HID; }
-    L.AGG = (uint16_t *)(act + a5[2]);
-    L.DUV = (uint16_t *)(act + a5[3]);
-    L.DH = (float *)(act + a5[4]);
-    L.DT = L.DH + (size_t)L.NP * HID;
-    L.DC = L.DT + (size_t)XP * HID;
-    return L;
+constexpr int kTrainThreads = 768;
+constexpr int kTrainWaves = kTrainThreads / 64;
+constexpr int kTrainParts = 3;  // wavefronts that share a weight-gradient tile, each a third of the nodes
+// The transposed weights come after the shared part.  At the end they and the activations make room
+// for every wavefront's gradients: kTrainParts copies of the nine matrices, then per wavefront the small
+// vectors and the loss.
+constexpr size_t kNetTransposed = sizeof(uint16_t) * 9 * 1024;
+constexpr size_t kNetFlush = sizeof(float) * (kTrainParts * 9 * 1024 + kTrainWaves * (SV_N + 1));
+__host__ __device__ inline size_t net_lds_act(size_t act) {
+    return act + kNetTransposed > al16(kNetFlush) ? act : al16(kNetFlush) - kNetTransposed;
 }
 
-// One 16x16 output tile: acc += A[16 x K] * B[K x 16], operands bf16 in LDS addressed by
-// strides (element (r,k) of A at A[r*ars + k*aks], element (k,c) of B at B[k*bks + c*bns]).
-// Lane layout of v_mfma_f32_16x16x16bf16_1k: lane l supplies A row (l & 15), k = 4(l >> 4)..+3,
-// B column (l & 15), same k; it receives D rows 4(l >> 4)..+3 of column (l & 15).
-__device__ __forceinline__ float4v mma16(const uint16_t *A, int ars, int aks, const uint16_t *B, int bks, int bns,
-                                         int K, float4v acc, int lane) {
-    const int r = lane & 15, kq = (lane >> 4) * 4;
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        short4v a, b;
-#pragma unroll
-        for (int t = 0; t < 4; t++) {
-            a[t] = (short)A[r * ars + (k0 + kq + t) * aks];
-            b[t] = (short)B[(k0 + kq + t) * bks + r * bns];
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-    }
-    return acc;
-}
+// Feature rows of 32 bf16: the 8-byte group q4 (4 features) of row v sits at position
+// q4 ^ ((v >> 1) & 7), so 16 consecutive rows' reads of one group, and reads and writes of whole rows,
+// spread over the LDS banks.  Byte offsets of a group and of one feature.
+__device__ __forceinline__ int row8(int v, int q4) { return v * 64 + ((q4 ^ ((v >> 1) & 7)) << 3); }
+__device__ __forceinline__ int row2(int v, int f) { return row8(v, f >> 2) + (f & 3) * 2; }
+// Rows of 32 floats: the 16-byte group q4 at the same position.  A row's offset with group 0's position
+// (row8(v, 0), and twice it for floats) gives every group's by an exclusive or with q4 << 3 (<< 4).
+__device__ __forceinline__ int frow(int v, int q4) { return 2 * row8(v, q4); }
 
-__device__ __forceinline__ const uint16_t *Wmat(const NetLds &L, int layer, int which) {  // which: 0 A, 1 B, 2 C
-    return L.wbf + ((size_t)(layer - 1) * 3 + which) * 1024;
+__device__ __forceinline__ float4v unpack4(uint2 u) {
+    return (float4v){__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                     __uint_as_float(u.y & 0xffff0000u)};
 }
+__device__ __forceinline__ uint2 pack4(float4v v) { return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])); }
 
-// Mean over the neighbours: dst[node][f] = (1/deg) sum src[nb][f]; rows >= count zero-filled.
-__device__ void mean_checks(const NetLds &L, const uint16_t *Hsrc, uint16_t *dst) {  // per check over its faults
-    for (int it = threadIdx.x; it < L.MP * HID; it += kNetThreads) {
-        const int i = it >> 5, f = it & 31;
-        float s = 0.f;
-        if (i < L.m) {
-            const int e0 = L.rp[i], e1 = L.rp[i + 1];
-            for (int e = e0; e < e1; e++) s += bf2f(Hsrc[L.ci[e] * HID + f]);
-            if (e1 > e0) s *= 1.0f / (float)(e1 - e0);
-        }
-        dst[it] = f2bf(s);
-    }
-}
-__device__ void mean_faults(const NetLds &L, const uint16_t *Csrc, uint16_t *dst) {  // per fault over its checks
-    for (int it = threadIdx.x; it < L.NP * HID; it += kNetThreads) {
-        const int j = it >> 5, f = it & 31;
-        float s = 0.f;
-        if (j < L.n) {
-            const int c0 = L.cp[j], c1 = L.cp[j + 1];
-            for (int c = c0; c < c1; c++) s += bf2f(Csrc[L.ri[c] * HID + f]);
-            if (c1 > c0) s *= 1.0f / (float)(c1 - c0);
-        }
-        dst[it] = f2bf(s);
-    }
-}
+// Forward and backward of one shot at a time on one workgroup of 12 wavefronts; LDSACT: the activations
+// sit in LDS.  Dense products are pairs of v_mfma_f32_16x16x16_bf16 (features 0..15, then 16..31),
+// formed transposed (D = W X^T) so a lane receives four consecutive features of one node and stores
+// them as one word; a lane's operand, two groups of four features of one node, is gathered from the
+// node's neighbours, averaged in float32 and rounded to bf16 in registers (forward), or read as two
+// words.  Weight gradients sum over nodes: their operands are
+// columns of the feature rows, and the tiles (one of B or C and one of A per wavefront and layer, the
+// nodes split over two or four wavefronts) stay in registers across all shots of the workgroup.  The
+// vectors' gradients stay in registers too: a thread always works on the same four features.
+//
+// A shot is bound by the latency of its phases (two per layer forward, four backward, of 1.6 to 4.4
+// thousand cycles each with three wavefronts per SIMD; 12 wavefronts leave each 168 registers, enough
+// for all gradients: 16 of 128 spilled and were slower), about 21 us; the prologue and the flush take
+// 17 us a workgroup.  Gradient of 1,024 shots of [[144,12,12]]: 1.02 ms -> 0.113 ms (before: 4
+// wavefronts, float atomics on LDS, four cycles a lane, for every element of the vectors' gradients,
+// 2-byte operand reads and a tanh per feature).  256 shots of the 936 x 8800 detector error model with
+// activations in the workspace: 28.1 -> 4.9 ms.
 
-// Forward pass of one shot; Hb[0..3], Cb[1..3] hold the activations afterwards.
-__device__ void forward_shot(const NetLds &L, const uint8_t *syn, int lane, int wave) {
-    // input layer
-    for (int it = threadIdx.x; it < L.NP * HID; it += kNetThreads) {
-        const int j = it >> 5, f = it & 31;
-        float h = 0.f;
-        if (j < L.n) {
-            const float x0 = tanhf(L.Lsh[j] * 0.125f), x1 = L.lam[j] * 0.125f;
-            h = fmaxf(L.sv[SV_W0 + f * 2] * x0 + L.sv[SV_W0 + f * 2 + 1] * x1 + L.sv[SV_B0 + f], 0.f);
-        }
-        L.Hb[0][it] = f2bf(h);
-    }
-    __syncthreads();
-    for (int l = 1; l <= NL; l++) {
-        mean_checks(L, L.Hb[l - 1], L.AGG);
-        __syncthreads();
-        // c = relu(A m + sigma a)
-        for (int tile = wave; tile < (L.MP / 16) * 2; tile += 4) {
-            const int rt = tile >> 1, ct = tile & 1;
-            float4v acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mma16(L.AGG + rt * 16 * HID, HID, 1, Wmat(L, l, 0) + ct * 16 * HID, 1, HID, HID, acc, lane);
-            const int col = ct * 16 + (lane & 15);
-#pragma unroll
-            for (int t = 0; t < 4; t++) {
-                const int row = rt * 16 + (lane >> 4) * 4 + t;
-                float v = 0.f;
-                if (row < L.m) {
-                    const float sg = (syn[row] & 1) ? -1.f : 1.f;
-                    v = fmaxf(acc[t] + sg * L.sv[SV_A + (l - 1) * HID + col], 0.f);
-                }
-                L.Cb[l][row * HID + col] = f2bf(v);
-            }
-        }
-        __syncthreads();
-        mean_faults(L, L.Cb[l], L.AGG);
-        __syncthreads();
-        // h = relu(B h + C g + b)
-        for (int tile = wave; tile < (L.NP / 16) * 2; tile += 4) {
-            const int rt = tile >> 1, ct = tile & 1;
-            float4v acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mma16(L.Hb[l - 1] + rt * 16 * HID, HID, 1, Wmat(L, l, 1) + ct * 16 * HID, 1, HID, HID, acc, lane);
-            acc = mma16(L.AGG + rt * 16 * HID, HID, 1, Wmat(L, l, 2) + ct * 16 * HID, 1, HID, HID, acc, lane);
-            const int col = ct * 16 + (lane & 15);
-#pragma unroll
-            for (int t = 0; t < 4; t++) {
-                const int row = rt * 16 + (lane >> 4) * 4 + t;
-                const float v = row < L.n ? fmaxf(acc[t] + L.sv[SV_BL + (l - 1) * HID + col], 0.f) : 0.f;
-                L.Hb[l][row * HID + col] = f2bf(v);
-            }
-        }
-        __syncthreads();
-    }
-}
-
-__device__ __forceinline__ float delta_of(const NetLds &L, int j) {
-    float d = L.sv[SV_BO];
-    const uint16_t *h = L.Hb[NL] + j * HID;
-#pragma unroll
-    for (int f = 0; f < HID; f++) d += L.sv[SV_W + f] * bf2f(h[f]);
-    return d;
-}
-
-__global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs A) {
+// DR, DC: every check has DR faults and every fault DC checks, so a node's neighbours are read
+// together; 0: the degrees come from the tables.
+template <bool LDSACT, int DR, int DC>
+__global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int n = A.g.n, m = A.g.m, E = A.g.nnz;
-    const bool train = A.train != 0;
-    size_t so[5];
-    const size_t shared_bytes = net_shared_layout(n, m, E, train, so);
-    unsigned char *act = A.act ? A.act + (size_t)blockIdx.x * A.act_stride : smem + shared_bytes;
-    NetLds L = carve_net(smem, act, n, m, E, train, A.lam);
+    const int NP = pad16(n), MP = pad16(m), XP = NP > MP ? NP : MP;
+    size_t so[5], ao[5];
+    const size_t shared_bytes = net_shared_layout(n, m, E, true, so);
+    net_act_layout(n, m, ao);
+    unsigned char *wrow = smem + so[0];  // [layer][A,B,C][out] rows of 32 inputs, as feature rows
+    float *sv = (float *)(smem + so[1]);
+    uint16_t *rp = (uint16_t *)(smem + so[3]), *ci = rp + (m + 1), *cp = ci + E, *ri = cp + (n + 1);
+    float *loss = (float *)(smem + so[4]);
+    unsigned char *wcol = smem + shared_bytes;  // LDSACT: [layer][A,B,C][in] rows of 32 outputs
+    unsigned char *act;
+    if constexpr (LDSACT) act = smem + shared_bytes + kNetTransposed;
+    else act = A.act + (size_t)blockIdx.x * A.act_stride;
+    float *Lsh = (float *)(act + ao[0]), *x0 = Lsh + n, *x1 = x0 + n, *ev = x1 + n, *rdf = ev + n, *sgn = rdf + n, *rdc = sgn + m;
+    auto Hrow = [&](int l) { return act + ao[1] + (size_t)l * NP * 64; };
+    auto Crow = [&](int l) { return act + ao[1] + (size_t)(NL + 1) * NP * 64 + (size_t)(l - 1) * MP * 64; };
+    unsigned char *AGG = act + ao[2], *DUV = act + ao[3], *DH = act + ao[4], *DT = DH + (size_t)NP * 128;
 
-    // weights: 32x32 matrices as bf16, vectors as float
-    for (int x = t; x < 9 * 1024; x += kNetThreads) {
-        const int mat = x >> 10, layer = mat / 3, which = mat % 3;
-        const int off = P_LAYER + layer * P_LSTRIDE + (which == 0 ? P_A : which == 1 ? P_B : P_C) + (x & 1023);
-        L.wbf[x] = f2bf(A.theta[off]);
+    // every load of the prologue is issued before the first result is used
+    constexpr int TH = 9 * 1024 / kTrainThreads;
+    static_assert(TH * kTrainThreads == 9 * 1024 && kTrainThreads >= SV_N, "one pass over the parameters");
+    auto matrix_offset = [](int mat) { return P_LAYER + (mat / 3) * P_LSTRIDE + (mat % 3 == 0 ? P_A : mat % 3 == 1 ? P_B : P_C); };
+    float th[TH];
+#pragma unroll
+    for (int k = 0; k < TH; k++) {
+        const int x = t + k * kTrainThreads;
+        th[k] = A.theta[matrix_offset(x >> 10) + (x & 1023)];
     }
-    for (int x = t; x < SV_N; x += kNetThreads) {
-        float v;
-        if (x < SV_B0) v = A.theta[P_W0 + x];
-        else if (x < SV_A) v = A.theta[P_B0 + (x - SV_B0)];
-        else if (x < SV_BL) { const int l = (x - SV_A) >> 5; v = A.theta[P_LAYER + l * P_LSTRIDE + P_a + ((x - SV_A) & 31)]; }
-        else if (x < SV_W) { const int l = (x - SV_BL) >> 5; v = A.theta[P_LAYER + l * P_LSTRIDE + P_b + ((x - SV_BL) & 31)]; }
-        else if (x < SV_BO) v = A.theta[P_W + (x - SV_W)];
-        else v = A.theta[P_BO];
-        L.sv[x] = v;
-        if (train) L.svg[x] = 0.f;
+    auto offset_of = [](int x) {  // parameter offset of small-vector entry x
+        if (x < SV_B0) return P_W0 + x;
+        if (x < SV_A) return P_B0 + (x - SV_B0);
+        if (x < SV_BL) return P_LAYER + ((x - SV_A) >> 5) * P_LSTRIDE + P_a + ((x - SV_A) & 31);
+        if (x < SV_W) return P_LAYER + ((x - SV_BL) >> 5) * P_LSTRIDE + P_b + ((x - SV_BL) & 31);
+        if (x < SV_BO) return P_W + (x - SV_W);
+        return P_BO;
+    };
+    // LDSACT: the tables of neighbours hold their rows' offsets (row8(v, 0), below 2^16)
+    auto entry = [](int v) { return (uint16_t)(LDSACT ? row8(v, 0) : v); };
+    const float svt = t < SV_N ? A.theta[offset_of(t)] : 0.f;
+    for (int x = t; x < E; x += kTrainThreads) {
+        const int c = A.g.col_idx[x], r = A.g.row_idx[x];
+        ci[x] = entry(c);
+        ri[x] = entry(r);
     }
-    for (int x = t; x <= m; x += kNetThreads) L.rp[x] = (uint16_t)A.g.row_ptr[x];
-    for (int x = t; x < E; x += kNetThreads) L.ci[x] = (uint16_t)A.g.col_idx[x];
-    for (int x = t; x <= n; x += kNetThreads) L.cp[x] = (uint16_t)A.g.col_ptr[x];
-    for (int x = t; x < E; x += kNetThreads) L.ri[x] = (uint16_t)A.g.row_idx[x];
-    if (t == 0) L.misc[0] = 0.f;
+    for (int x = t; x <= m; x += kTrainThreads) rp[x] = (uint16_t)A.g.row_ptr[x];
+    for (int x = t; x <= n; x += kTrainThreads) cp[x] = (uint16_t)A.g.col_ptr[x];
+    for (int j = t; j < n; j += kTrainThreads) x1[j] = A.lam[j] * 0.125f;
+#pragma unroll
+    for (int k = 0; k < TH; k++) {
+        const int x = t + k * kTrainThreads, mat = x >> 10, o = (x >> 5) & 31, i = x & 31;
+        const uint16_t w = f2bf(th[k]);
+        *(uint16_t *)(wrow + row2(mat * 32 + o, i)) = w;
+        if constexpr (LDSACT) *(uint16_t *)(wcol + row2(mat * 32 + i, o)) = w;
+    }
+    if (t < SV_N) sv[t] = svt;
     __syncthreads();
+    for (int j = t; j < n; j += kTrainThreads) rdf[j] = cp[j + 1] > cp[j] ? 1.0f / (float)(cp[j + 1] - cp[j]) : 0.f;
+    for (int i = t; i < m; i += kTrainThreads) rdc[i] = rp[i + 1] > rp[i] ? 1.0f / (float)(rp[i + 1] - rp[i]) : 0.f;
+    if (t == 0) loss[0] = 0.f;
 
-    // weight-gradient tiles kept in registers: wavefront w owns tile (w >> 1, w & 1) of each
-    // of the nine matrices [layer][A,B,C]
-    float4v gacc[9];
+    int tv = t;                 // the thread, opaque to the compiler from layer to layer: the offsets that
+                                // depend on it only are cheaper to form again than to keep in registers
+    int nl = lane & 15, kq = lane >> 4;  // products: node (or row) and group of the k range
+    int q4 = t & 7;                      // elementwise phases: this thread's four features
+    auto renew = [&]() {
+        asm volatile("" : "+v"(tv));
+        nl = tv & 15;
+        kq = (tv >> 4) & 3;
+        q4 = tv & 7;
+    };
+    const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
+    // operand: features 4 kq .. + 3 and 16 + 4 kq .. + 3 of one row
+    struct Op { uint2 lo, hi; };
+    const Op zero_op = {make_uint2(0u, 0u), make_uint2(0u, 0u)};
+    auto load_op = [&](const unsigned char *rows, int v) {
+        return Op{*(const uint2 *)(rows + row8(v, kq)), *(const uint2 *)(rows + row8(v, kq + 4))};
+    };
+    // operand rows of W^T (inputs ct 16 .. + 15, k = outputs)
+    auto wt_op = [&](int mat, int ct) -> Op {
+        if constexpr (LDSACT) {
+            return load_op(wcol, mat * 32 + ct * 16 + nl);
+        } else {
+            uint32_t h[8];
 #pragma unroll
-    for (int q = 0; q < 9; q++) gacc[q] = (float4v){0.f, 0.f, 0.f, 0.f};
-    const int trow = (wave >> 1) * 16, tcol = (wave & 1) * 16;
-
-    const int total = A.list ? *A.list_count : A.count;
-    for (int item = blockIdx.x; item < total; item += gridDim.x) {
-        const int shot = A.list ? A.list[item] : item;
-        const uint8_t *syn = A.syn + (size_t)shot * m;
-        const float *llr = A.llr + (size_t)shot * n;
-        for (int j = t; j < n; j += kNetThreads) L.Lsh[j] = llr[j];
-        __syncthreads();
-        forward_shot(L, syn, lane, wave);
-
-        if (!train) {
-            for (int j = t; j < n; j += kNetThreads) A.llr_out[(size_t)shot * n + j] = L.Lsh[j] + delta_of(L, j);
-            __syncthreads();
-            continue;
+            for (int u = 0; u < 8; u++)
+                h[u] = *(const uint16_t *)(wrow + row2(mat * 32 + (u >> 2) * 16 + kq * 4 + (u & 3), ct * 16 + nl));
+            return Op{make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16), make_uint2(h[4] | h[5] << 16, h[6] | h[7] << 16)};
         }
-
-        // ---- loss and output layer
-        const uint8_t *err = A.err + (size_t)shot * n;
-        for (int it = t; it < L.NP * HID; it += kNetThreads) L.DH[it] = 0.f;
-        __syncthreads();
-        for (int j = t; j < n; j += kNetThreads) {
-            const float Lp = L.Lsh[j] + delta_of(L, j);
-            const float e = (float)(err[j] & 1);
-            // softplus(-L') + e L'
-            const float lossj = fmaxf(-Lp, 0.f) + log1pf(expf(-fabsf(Lp))) + e * Lp;
-            atomicAdd(&L.misc[0], lossj * A.inv_total);
-            const float dD = (e - 1.f / (1.f + expf(Lp))) * A.inv_total;
-            atomicAdd(&L.svg[SV_BO], dD);
-            const uint16_t *h = L.Hb[NL] + j * HID;
-            for (int f = 0; f < HID; f++) {
-                atomicAdd(&L.svg[SV_W + f], dD * bf2f(h[f]));
-                L.DH[j * HID + f] = dD * L.sv[SV_W + f];
-            }
-        }
-        __syncthreads();
-        for (int l = NL; l >= 1; l--) {
-            // du = dh * [h_l > 0]; db_l; g_l recomputed into AGG
-            for (int it = t; it < L.NP * HID; it += kNetThreads) {
-                const float du = bf2f(L.Hb[l][it]) > 0.f ? L.DH[it] : 0.f;
-                L.DUV[it] = f2bf(du);
-                if (du != 0.f) atomicAdd(&L.svg[SV_BL + (l - 1) * HID + (it & 31)], du);
-            }
-            mean_faults(L, L.Cb[l], L.AGG);
-            __syncthreads();
-            // dB += du^T h_{l-1}, dC += du^T g  (K = faults)
-            gacc[(l - 1) * 3 + 1] = mma16(L.DUV + trow, 1, HID, L.Hb[l - 1] + tcol, HID, 1, L.NP,
-                                          gacc[(l - 1) * 3 + 1], lane);
-            gacc[(l - 1) * 3 + 2] = mma16(L.DUV + trow, 1, HID, L.AGG + tcol, HID, 1, L.NP, gacc[(l - 1) * 3 + 2], lane);
-            // dg = du C -> DT, dh_{l-1} = du B -> DH
-            for (int tile = wave; tile < (L.NP / 16) * 4; tile += 4) {
-                const int rt = tile >> 2, which = (tile >> 1) & 1, ct = tile & 1;
-                float4v acc = {0.f, 0.f, 0.f, 0.f};
-                acc = mma16(L.DUV + rt * 16 * HID, HID, 1, Wmat(L, l, which == 0 ? 2 : 1) + ct * 16, HID, 1, HID, acc,
-                            lane);
-                float *dst = which == 0 ? L.DT : L.DH;
-                const int col = ct * 16 + (lane & 15);
+    };
+    auto product = [](const Op &w, const Op &x, float4v acc) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, w.lo), __builtin_bit_cast(short4v, x.lo), acc, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, w.hi), __builtin_bit_cast(short4v, x.hi), acc, 0, 0, 0);
+    };
+    // sum of f(neighbour's row offset) over a node's neighbours, in their order; ROWS: neighbours of a
+    // check, else of a fault
+    auto row_of = [](int v) { return LDSACT ? v : row8(v, 0); };  // offset of a table entry's row
+    auto over = [&](auto Rows, int v, auto &&load, auto &&add) {
+        constexpr bool ROWS = decltype(Rows)::value;
+        constexpr int D = ROWS ? DR : DC;
+        const uint16_t *idx = ROWS ? ci : ri;
+        if constexpr (D > 0) {
+            decltype(load(0)) x[D];
 #pragma unroll
-                for (int q = 0; q < 4; q++) dst[(rt * 16 + (lane >> 4) * 4 + q) * HID + col] = acc[q];
+            for (int u = 0; u < D; u++) x[u] = load(row_of(idx[v * D + u]));
+#pragma unroll
+            for (int u = 0; u < D; u++) add(x[u]);
+        } else {
+            const int e1 = ROWS ? rp[v + 1] : cp[v + 1];
+            for (int e = ROWS ? rp[v] : cp[v]; e < e1; e++) add(load(row_of(idx[e])));
+        }
+    };
+    using Checks = std::true_type;   // over a check's faults
+    using Faults = std::false_type;  // over a fault's checks
+    // neighbour means: 4 features of one node (elementwise phases), an operand (products)
+    auto mean4 = [&](auto Rows, const unsigned char *rows, int v, float rd) {
+        float4v s = zero4;
+        over(Rows, v, [&](int r) { return *(const uint2 *)(rows + (r ^ (q4 << 3))); }, [&](uint2 x) { s += unpack4(x); });
+        return s * rd;
+    };
+    auto mean_op = [&](auto Rows, const unsigned char *rows, int v, float rd) {
+        float4v a = zero4, b = zero4;
+        over(Rows, v,
+             [&](int r) { return Op{*(const uint2 *)(rows + (r ^ (kq << 3))), *(const uint2 *)(rows + (r ^ ((kq + 4) << 3)))}; },
+             [&](const Op &x) {
+                 a += unpack4(x.lo);
+                 b += unpack4(x.hi);
+             });
+        return Op{pack4(a * rd), pack4(b * rd)};
+    };
+    // 16 x 16 tiles of weight gradients over the nodes of steps s0, s0 + kTrainParts, ...: rows from the
+    // masked gradient's features, columns from the aggregation and, with a second accumulator, from
+    // feature rows.
+    const int gs = XP + 4;  // nodes per feature of the aggregation (the pad spreads it over the banks)
+    auto wgrad = [&](int trow, int tcol, int steps, int s0, float4v &acc, auto Two, const unsigned char *rows, float4v &acc2) {
+        constexpr bool TWO = decltype(Two)::value;
+        for (int s = s0; s < steps; s += kTrainParts) {
+            const int v = s * 16 + kq * 4;
+            short4v a, c;
+#pragma unroll
+            for (int u = 0; u < 4; u++) a[u] = *(const short *)(DUV + row2(v + u, trow + nl));
+            const short4v b = *(const short4v *)((const uint16_t *)AGG + (tcol + nl) * gs + v);
+            if constexpr (TWO) {
+#pragma unroll
+                for (int u = 0; u < 4; u++) c[u] = *(const short *)(rows + row2(v + u, tcol + nl));
             }
-            __syncthreads();
-            // dc_i = sum_{j in N(i)} dg_j / deg_j
-            for (int it = t; it < L.MP * HID; it += kNetThreads) {
-                const int i = it >> 5, f = it & 31;
-                float s = 0.f;
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+            if constexpr (TWO) acc2 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, c, acc2, 0, 0, 0);
+        }
+    };
+    auto put_agg = [&](int v, float4v x) {
+        const uint2 p = pack4(x);
+        uint16_t *d = (uint16_t *)AGG + q4 * 4 * gs + v;
+        d[0] = (uint16_t)p.x;
+        d[gs] = (uint16_t)(p.x >> 16);
+        d[2 * gs] = (uint16_t)p.y;
+        d[3 * gs] = (uint16_t)(p.y >> 16);
+    };
+    // wavefront w's tiles: dB of tile w & 3 and dC of the same, dA likewise, part w >> 2
+    static_assert(kTrainWaves == 4 * kTrainParts, "four tiles a matrix");
+    const int g_row = ((wave >> 1) & 1) * 16, g_col = (wave & 1) * 16, g_part = wave >> 2;
+    float4v gb[NL], gc[NL], ga[NL], accb[NL], acca[NL], accw = zero4, accb0 = zero4, accx0 = zero4, accx1 = zero4;
+    float accbo = 0.f, accloss = 0.f;
+#pragma unroll
+    for (int l = 0; l < NL; l++) gb[l] = gc[l] = ga[l] = accb[l] = acca[l] = zero4;
+
+    // LDSACT (no more faults or checks than threads): the next shot's inputs are in flight while this one runs
+    float nx_llr = 0.f;
+    int nx_err = 0, nx_syn = 0;
+    auto fetch = [&](int shot) {
+        if (shot >= A.count) return;
+        if (t < n) {
+            nx_llr = A.llr[(size_t)shot * n + t];
+            nx_err = A.err[(size_t)shot * n + t];
+        }
+        if (t < m) nx_syn = A.syn[(size_t)shot * m + t];
+    };
+    if constexpr (LDSACT) fetch(blockIdx.x);
+    for (int shot = blockIdx.x; shot < A.count; shot += gridDim.x) {
+        __syncthreads();  // the previous shot's buffers, or the tables
+        auto put_fault = [&](int j, float v, int e) {
+            Lsh[j] = v;
+            x0[j] = tanhf(v * 0.125f);
+            ev[j] = (float)(e & 1);
+        };
+        if constexpr (LDSACT) {
+            if (t < n) put_fault(t, nx_llr, nx_err);
+            if (t < m) sgn[t] = (nx_syn & 1) ? -1.f : 1.f;
+            fetch(shot + gridDim.x);
+        } else {
+            for (int j = t; j < n; j += kTrainThreads)
+                put_fault(j, A.llr[(size_t)shot * n + j], A.err[(size_t)shot * n + j]);
+            for (int i = t; i < m; i += kTrainThreads) sgn[i] = (A.syn[(size_t)shot * m + i] & 1) ? -1.f : 1.f;
+        }
+        __syncthreads();
+        renew();
+        // ---- forward: input layer
+        for (int it = tv; it < NP * 8; it += kTrainThreads) {
+            const int j = it >> 3;
+            float4v h = zero4;
+            if (j < n) {
+                const float a = x0[j], b = x1[j];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const int f = q4 * 4 + u;
+                    h[u] = fmaxf(sv[SV_W0 + f * 2] * a + sv[SV_W0 + f * 2 + 1] * b + sv[SV_B0 + f], 0.f);
+                }
+            }
+            *(uint2 *)(Hrow(0) + row8(j, q4)) = pack4(h);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int l = 1; l <= NL; l++) {
+            const int mat = (l - 1) * 3;
+            renew();
+            // c = relu(A mean(h) + sigma a)
+            for (int tile = wave; tile < MP / 16; tile += kTrainWaves) {
+                const int i = tile * 16 + nl;
+                Op x = zero_op;
+                float sg = 0.f;
                 if (i < m) {
-                    for (int e = L.rp[i]; e < L.rp[i + 1]; e++) {
-                        const int j = L.ci[e];
-                        s += L.DT[j * HID + f] / (float)(L.cp[j + 1] - L.cp[j]);
-                    }
+                    x = mean_op(Checks{}, Hrow(l - 1), i, rdc[i]);
+                    sg = sgn[i];
                 }
-                L.DC[it] = s;
-            }
-            __syncthreads();
-            // dv = dc * [c > 0]; da; m_l recomputed into AGG
-            for (int it = t; it < L.MP * HID; it += kNetThreads) {
-                const int i = it >> 5;
-                const float dv = bf2f(L.Cb[l][it]) > 0.f ? L.DC[it] : 0.f;
-                L.DUV[it] = f2bf(dv);
-                if (dv != 0.f) atomicAdd(&L.svg[SV_A + (l - 1) * HID + (it & 31)], (syn[i] & 1) ? -dv : dv);
-            }
-            mean_checks(L, L.Hb[l - 1], L.AGG);
-            __syncthreads();
-            // dA += dv^T m (K = checks); dm = dv A -> DT
-            gacc[(l - 1) * 3 + 0] = mma16(L.DUV + trow, 1, HID, L.AGG + tcol, HID, 1, L.MP, gacc[(l - 1) * 3 + 0], lane);
-            for (int tile = wave; tile < (L.MP / 16) * 2; tile += 4) {
-                const int rt = tile >> 1, ct = tile & 1;
-                float4v acc = {0.f, 0.f, 0.f, 0.f};
-                acc = mma16(L.DUV + rt * 16 * HID, HID, 1, Wmat(L, l, 0) + ct * 16, HID, 1, HID, acc, lane);
-                const int col = ct * 16 + (lane & 15);
 #pragma unroll
-                for (int q = 0; q < 4; q++) L.DT[(rt * 16 + (lane >> 4) * 4 + q) * HID + col] = acc[q];
+                for (int ct = 0; ct < 2; ct++) {
+                    const float4v d = product(load_op(wrow, mat * 32 + ct * 16 + nl), x, zero4);
+                    const float4v a = *(const float4v *)(sv + SV_A + (l - 1) * HID + ct * 16 + kq * 4);
+                    float4v c;
+#pragma unroll
+                    for (int u = 0; u < 4; u++) c[u] = i < m ? fmaxf(d[u] + sg * a[u], 0.f) : 0.f;
+                    *(uint2 *)(Crow(l) + row8(i, ct * 4 + kq)) = pack4(c);
+                }
             }
             __syncthreads();
-            // dh_{l-1} += sum_{i in N(j)} dm_i / deg_i
-            for (int it = t; it < L.NP * HID; it += kNetThreads) {
-                const int j = it >> 5, f = it & 31;
-                if (j < n) {
-                    float s = 0.f;
-                    for (int c = L.cp[j]; c < L.cp[j + 1]; c++) {
-                        const int i = L.ri[c];
-                        s += L.DT[i * HID + f] / (float)(L.rp[i + 1] - L.rp[i]);
+            renew();
+            // h = relu(B h + C mean(c) + b)
+            for (int tile = wave; tile < NP / 16; tile += kTrainWaves) {
+                const int j = tile * 16 + nl;
+                Op x = zero_op;
+                if (j < n) x = mean_op(Faults{}, Crow(l), j, rdf[j]);
+                const Op h = load_op(Hrow(l - 1), j);
+                float out = 0.f;
+#pragma unroll
+                for (int ct = 0; ct < 2; ct++) {
+                    float4v d = product(load_op(wrow, (mat + 1) * 32 + ct * 16 + nl), h, zero4);
+                    d = product(load_op(wrow, (mat + 2) * 32 + ct * 16 + nl), x, d);
+                    const float4v b = *(const float4v *)(sv + SV_BL + (l - 1) * HID + ct * 16 + kq * 4);
+                    float4v r;
+#pragma unroll
+                    for (int u = 0; u < 4; u++) r[u] = j < n ? fmaxf(d[u] + b[u], 0.f) : 0.f;
+                    const uint2 p = pack4(r);
+                    *(uint2 *)(Hrow(l) + row8(j, ct * 4 + kq)) = p;
+                    if (l == NL) {
+                        const float4v h4 = unpack4(p), w4 = *(const float4v *)(sv + SV_W + ct * 16 + kq * 4);
+                        out += h4[0] * w4[0] + h4[1] * w4[1] + h4[2] * w4[2] + h4[3] * w4[3];
                     }
-                    L.DH[it] += s;
+                }
+                if (l == NL) {
+                    // L' = L + w . h + b_out over the fault's four lanes; loss and its gradient
+                    out += __shfl_xor(out, 16, 64);
+                    out += __shfl_xor(out, 32, 64);
+                    if (kq == 0 && j < n) {
+                        const float Lp = Lsh[j] + (out + sv[SV_BO]), e = ev[j];
+                        // softplus(-L') + e L'
+                        accloss += (fmaxf(-Lp, 0.f) + log1pf(expf(-fabsf(Lp))) + e * Lp) * A.inv_total;
+                        const float dD = (e - 1.f / (1.f + expf(Lp))) * A.inv_total;
+                        accbo += dD;
+                        Lsh[j] = dD;
+                    }
                 }
             }
             __syncthreads();
         }
-        // input layer
-        for (int it = t; it < n * HID; it += kNetThreads) {
-            const int j = it >> 5, f = it & 31;
-            if (bf2f(L.Hb[0][it]) > 0.f) {
-                const float du = L.DH[it];
-                const float x0 = tanhf(L.Lsh[j] * 0.125f), x1 = L.lam[j] * 0.125f;
-                atomicAdd(&L.svg[SV_W0 + f * 2], du * x0);
-                atomicAdd(&L.svg[SV_W0 + f * 2 + 1], du * x1);
-                atomicAdd(&L.svg[SV_B0 + f], du);
+        // ---- backward.  Per layer: the gradient of the fault features (from the output layer, or the
+        // product with B plus the neighbour sum of the layer above), masked; g recomputed; then the
+        // products, and the same on the checks' side.
+        const float4v wv = *(const float4v *)(sv + SV_W + q4 * 4);
+#pragma unroll
+        for (int l = NL; l >= 0; l--) {
+            renew();
+            for (int it = tv; it < NP * 8; it += kTrainThreads) {
+                const int j = it >> 3;
+                float4v dh = zero4, h = unpack4(*(const uint2 *)(Hrow(l) + row8(j, q4)));
+                if (l == NL) {
+                    if (j < n) {
+                        const float dD = Lsh[j];
+                        accw += dD * h;
+                        dh = dD * wv;
+                    }
+                } else if (j < n) {
+                    float4v s = zero4;
+                    over(Faults{}, j, [&](int r) { return *(const float4v *)(DT + ((2 * r) ^ (q4 << 4))); },
+                         [&](float4v x) { s += x; });
+                    dh = *(const float4v *)(DH + frow(j, q4)) + s;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) dh[u] = h[u] > 0.f ? dh[u] : 0.f;
+                if (l == 0) {
+                    if (j < n) {
+                        accx0 += dh * x0[j];
+                        accx1 += dh * x1[j];
+                        accb0 += dh;
+                    }
+                } else {
+                    accb[l > 0 ? l - 1 : 0] += dh;
+                    *(uint2 *)(DUV + row8(j, q4)) = pack4(dh);
+                    float4v g = zero4;
+                    if (j < n) g = mean4(Faults{}, Crow(l > 0 ? l : 1), j, rdf[j]);
+                    put_agg(j, g);
+                }
             }
+            if (l == 0) break;
+            const int li = l > 0 ? l - 1 : 0, mat = li * 3;
+            __syncthreads();
+            renew();
+            // dB += du^T h_{l-1}, dC += du^T g; dg = du C -> DT, dh_{l-1} = du B -> DH
+            wgrad(g_row, g_col, NP / 16, g_part, gc[li], std::true_type{}, Hrow(li), gb[li]);
+            for (int tile = wave; tile < NP / 16; tile += kTrainWaves) {
+                const int j = tile * 16 + nl;
+                const Op du = load_op(DUV, j);
+                const float rd = j < n ? rdf[j] : 0.f;  // dc_i sums dg_j / deg_j
+#pragma unroll
+                for (int ct = 0; ct < 2; ct++) {
+                    *(float4v *)(DT + frow(j, ct * 4 + kq)) = product(wt_op(mat + 2, ct), du, zero4) * rd;
+                    *(float4v *)(DH + frow(j, ct * 4 + kq)) = product(wt_op(mat + 1, ct), du, zero4);
+                }
+            }
+            __syncthreads();
+            renew();
+            // dc_i = sum_{j in N(i)} dg_j / deg_j; dv = dc * [c > 0]; da; m_l recomputed into AGG
+            for (int it = tv; it < MP * 8; it += kTrainThreads) {
+                const int i = it >> 3;
+                float4v dv = zero4, mean = zero4;
+                if (i < m) {
+                    over(Checks{}, i, [&](int r) { return *(const float4v *)(DT + ((2 * r) ^ (q4 << 4))); },
+                         [&](float4v x) { dv += x; });
+                    const float4v c = unpack4(*(const uint2 *)(Crow(li + 1) + row8(i, q4)));
+#pragma unroll
+                    for (int u = 0; u < 4; u++) dv[u] = c[u] > 0.f ? dv[u] : 0.f;
+                    acca[li] += sgn[i] * dv;
+                    mean = mean4(Checks{}, Hrow(li), i, rdc[i]);
+                }
+                *(uint2 *)(DUV + row8(i, q4)) = pack4(dv);
+                put_agg(i, mean);
+            }
+            __syncthreads();
+            renew();
+            // dA += dv^T m; dm = dv A -> DT (summed over each fault's checks in the next phase)
+            wgrad(g_row, g_col, MP / 16, g_part, ga[li], std::false_type{}, nullptr, ga[li]);
+            for (int tile = wave; tile < MP / 16; tile += kTrainWaves) {
+                const int i = tile * 16 + nl;
+                const Op dv = load_op(DUV, i);
+                const float rd = i < m ? rdc[i] : 0.f;  // dh_j sums dm_i / deg_i
+#pragma unroll
+                for (int ct = 0; ct < 2; ct++)
+                    *(float4v *)(DT + frow(i, ct * 4 + kq)) = product(wt_op(mat, ct), dv, zero4) * rd;
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
-    if (!train) return;
-    // flush: matrix tiles (acc rows = out feature, cols = in feature), vectors, loss
+
+    // ---- flush: tiles (rows: out features, columns: in features), vectors, loss.  LDSACT: every
+    // wavefront stores its own, then the workgroup adds the copies and adds the sums to the global
+    // gradient (float atomics on LDS would take four cycles a lane: 43 us here).
+    float *parts = (float *)wcol, *vecs = parts + kTrainParts * 9 * 1024 + wave * (SV_N + 1);
+    if constexpr (LDSACT) __syncthreads();
+    auto add_tile = [&](int mat, float4v g) {
 #pragma unroll
-    for (int q = 0; q < 9; q++) {
-        const int layer = q / 3, which = q % 3;
-        const int base = P_LAYER + layer * P_LSTRIDE + (which == 0 ? P_A : which == 1 ? P_B : P_C);
-        const int col = tcol + (lane & 15);
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int row = trow + (lane >> 4) * 4 + r;
-            atomicAdd(&A.grad[base + row * HID + col], gacc[q][r]);
+        for (int u = 0; u < 4; u++) {
+            const int at = (g_row + kq * 4 + u) * HID + g_col + nl;
+            if constexpr (LDSACT) parts[(g_part * 9 + mat) * 1024 + at] = g[u];
+            else atomicAdd(&A.grad[matrix_offset(mat) + at], g[u]);
         }
+    };
+    auto add_vector = [&](int x, float v) {
+        if constexpr (LDSACT) vecs[x] = v;
+        else atomicAdd(&A.grad[offset_of(x)], v);
+    };
+#pragma unroll
+    for (int l = 0; l < NL; l++) {
+        add_tile(l * 3, ga[l]);
+        add_tile(l * 3 + 1, gb[l]);
+        add_tile(l * 3 + 2, gc[l]);
+    }
+    // the vectors: the wavefront's eight threads of each feature group, then one lane per group
+    auto flush4 = [&](int base, int stride, float4v v) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            v[u] += __shfl_xor(v[u], 8, 64);
+            v[u] += __shfl_xor(v[u], 16, 64);
+            v[u] += __shfl_xor(v[u], 32, 64);
+        }
+        if (lane < 8) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) add_vector(base + (q4 * 4 + u) * stride, v[u]);
+        }
+    };
+    flush4(SV_W0, 2, accx0);
+    flush4(SV_W0 + 1, 2, accx1);
+    flush4(SV_B0, 1, accb0);
+    flush4(SV_W, 1, accw);
+#pragma unroll
+    for (int l = 0; l < NL; l++) {
+        flush4(SV_A + l * HID, 1, acca[l]);
+        flush4(SV_BL + l * HID, 1, accb[l]);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        accloss += __shfl_xor(accloss, off, 64);
+        accbo += __shfl_xor(accbo, off, 64);
+    }
+    if (lane == 0) {
+        add_vector(SV_BO, accbo);
+        if constexpr (LDSACT) vecs[SV_N] = accloss;
+        else atomicAdd(loss, accloss);
     }
     __syncthreads();
-    for (int x = t; x < SV_N; x += kNetThreads) {
-        int off;
-        if (x < SV_B0) off = P_W0 + x;
-        else if (x < SV_A) off = P_B0 + (x - SV_B0);
-        else if (x < SV_BL) off = P_LAYER + ((x - SV_A) >> 5) * P_LSTRIDE + P_a + ((x - SV_A) & 31);
-        else if (x < SV_W) off = P_LAYER + ((x - SV_BL) >> 5) * P_LSTRIDE + P_b + ((x - SV_BL) & 31);
-        else if (x < SV_BO) off = P_W + (x - SV_W);
-        else off = P_BO;
-        atomicAdd(&A.grad[off], L.svg[x]);
+    if constexpr (LDSACT) {
+        // workgroups start at different places, so they do not queue on one address
+        constexpr int N = 9 * 1024 + SV_N + 1;
+        const int first = (int)((blockIdx.x * 64u * 37u) % (unsigned)N);
+        const float *vec0 = parts + kTrainParts * 9 * 1024;
+        for (int k = t; k < N; k += kTrainThreads) {
+            const int x = k + first < N ? k + first : k + first - N;
+            float s = 0.f;
+            if (x < 9 * 1024) {
+#pragma unroll
+                for (int c = 0; c < kTrainParts; c++) s += parts[c * 9 * 1024 + x];
+                atomicAdd(&A.grad[matrix_offset(x >> 10) + (x & 1023)], s);
+            } else {
+                const int y = x - 9 * 1024;
+#pragma unroll
+                for (int w = 0; w < kTrainWaves; w++) s += vec0[w * (SV_N + 1) + y];
+                atomicAdd(y < SV_N ? &A.grad[offset_of(y)] : A.loss, s);
+            }
+        }
+    } else if (t == 0) {
+        atomicAdd(A.loss, loss[0]);
     }
-    if (t == 0) atomicAdd(A.loss, L.misc[0]);
 }
 
 
@@ -452,7 +601,7 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs A) {
 //     A m_i = (1/deg_i) sum_{j in N(i)} A h_j,     C g_j = (1/deg_j) sum_{i in N(j)} C c_i,
 // so each neighbour's bf16 feature words feed the MFMA directly (no unpacking or vector sums)
 // and the 1/deg scaling is applied to the float32 accumulator.  Neighbour lists are padded to
-// the maximum degree with a zero sentinel row.  Compared with forward_shot (the training
+// the maximum degree with a zero sentinel row.  Compared with net_train_kernel (the training
 // forward) the means are not rounded to bf16 before the product; everything else matches.
 // ------------------------------------------------------------------------------------------
 constexpr int kInferWavesMax = 11;  // one workgroup of up to 11 wavefronts per CU, else 5 (two per CU)
@@ -1001,9 +1150,11 @@ __global__ __launch_bounds__(64 * kBigWaves) void net_infer_big_kernel(NetArgs A
     }
 }
 
-__global__ void zero_f32(float *p, int n) {
+// p[0 .. n) and *q
+__global__ void zero_f32(float *p, int n, float *q) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0.f;
+    else if (i == n) *q = 0.f;
 }
 
 __global__ void adam_kernel(float *theta, const float *grad, float *m1, float *m2, int n, float lr, float b1t, float b2t) {
@@ -1023,11 +1174,19 @@ static size_t net_shared_bytes(const DevGraph &g, bool train) {
     size_t o[5];
     return net_shared_layout(g.n, g.m, g.nnz, train, o);
 }
-static size_t net_act_bytes(const DevGraph &g, bool train) {
+static size_t net_act_bytes(const DevGraph &g) {
     size_t o[5];
-    return net_act_layout(g.n, g.m, train, o);
+    return net_act_layout(g.n, g.m, o);
 }
-size_t net_lds_bytes(const DevGraph &g, bool train) { return net_shared_bytes(g, train) + net_act_bytes(g, train); }
+// Training with the activations in LDS.
+static size_t net_train_lds(const DevGraph &g) {
+    return net_shared_bytes(g, true) + kNetTransposed + net_lds_act(net_act_bytes(g));
+}
+// ... which the kernel takes only where a thread covers each fault and each check of a shot, and a row's
+// offset fits 16 bits.
+static bool net_train_in_lds(const DevGraph &g) {
+    return net_train_lds(g) <= 159 * 1024 && std::max(pad16(g.n), pad16(g.m)) <= kTrainThreads;
+}
 
 // Wavefronts per inference workgroup: 11 in one workgroup when they fit in a CU's 160 KB of LDS
 // (11 wavefronts need 170 VGPRs or fewer: three per SIMD), else 5 (two workgroups per CU).
@@ -1083,27 +1242,31 @@ struct qlsd_net_s {
 };
 
 namespace qlsd {
-// Training, gradient and (for graphs the wave kernel cannot hold) inference launch of net_kernel:
-// one workgroup per shot at a time; activations in LDS or in the net's workspace slices.
-static hipError_t launch_net(qlsd_net_s *net, NetArgs a, int grid, hipStream_t st) {
-    const bool train = a.train != 0;
-    size_t lds = net_shared_bytes(a.g, train);
+// Gradient launch: one workgroup per shot at a time; activations in LDS or in the net's workspace
+// slices.
+static hipError_t launch_train(qlsd_net_s *net, NetArgs a, int grid, hipStream_t st) {
     if (net->act_stride && !net->d_act &&
         hipMalloc((void **)&net->d_act, net->act_stride * net->act_slices) != hipSuccess) {
         net->d_act = nullptr;
         return hipErrorOutOfMemory;
     }
+    size_t lds = net_train_lds(a.g);
     if (net->d_act) {
         a.act = net->d_act;
         a.act_stride = net->act_stride;
         grid = std::min(grid, net->act_slices);
-    } else {
-        lds += net_act_bytes(a.g, train);
+        lds = net_shared_bytes(a.g, true);
     }
-    hipError_t e = hipFuncSetAttribute((const void *)net_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(net_kernel, dim3(std::max(grid, 1)), dim3(kNetThreads), lds, st, a);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(std::max(grid, 1)), dim3(kTrainThreads), lds, st, a);
+        return hipGetLastError();
+    };
+    if (net->d_act) return go(net_train_kernel<false, 0, 0>);
+    const DevGraph &g = a.g;
+    const bool reg63 = g.min_rw == 6 && g.max_rw == 6 && g.min_cw == 3 && g.max_cw == 3;
+    return reg63 ? go(net_train_kernel<true, 6, 3>) : go(net_train_kernel<true, 0, 0>);
 }
 // Slices of the large-graph inference workspace: one per compute unit, so the grid's features
 // (about 0.7 MB per slice for the detector error model) stay in the last-level cache.
@@ -1183,8 +1346,8 @@ qlsd_status qlsd_net_create(qlsd_code code, const double *priors, const float *p
     net->num_cus = prop.multiProcessorCount;
     // wave-per-shot inference needs u16 byte offsets of feature rows (64 B each) and LDS room
     net->wave_infer = pad16(g.n) + 1 <= 1023 && pad16(g.m) + 1 <= 1023 && infer_lds_bytes(g) <= 160 * 1024;
-    if (net_lds_bytes(g, true) > 159 * 1024) {  // training activations in a device workspace (allocated at first use)
-        net->act_stride = (net_act_bytes(g, true) + 255) & ~size_t(255);
+    if (!net_train_in_lds(g)) {  // training activations in a device workspace (allocated at first use)
+        net->act_stride = (net_act_bytes(g) + 255) & ~size_t(255);
         net->act_slices = net->num_cus;
     }
     if (!net->wave_infer) {
@@ -1283,8 +1446,7 @@ qlsd_status qlsd_net_forward(qlsd_net net, const uint8_t *syndromes, const float
 
 static qlsd_status grad_impl(qlsd_net net, const uint8_t *syn, const float *llr, const uint8_t *err, int32_t B,
                              float *grad, float *loss, hipStream_t st) {
-    hipLaunchKernelGGL(zero_f32, dim3((NPAR + 255) / 256), dim3(256), 0, st, grad, NPAR);
-    hipLaunchKernelGGL(zero_f32, dim3(1), dim3(64), 0, st, loss, 1);
+    hipLaunchKernelGGL(zero_f32, dim3((NPAR + 1 + 255) / 256), dim3(256), 0, st, grad, NPAR, loss);
     NetArgs a = net_args(net);
     a.syn = syn;
     a.llr = llr;
@@ -1293,9 +1455,8 @@ static qlsd_status grad_impl(qlsd_net net, const uint8_t *syn, const float *llr,
     a.grad = grad;
     a.loss = loss;
     a.inv_total = 1.f / ((float)B * (float)net->g.n);
-    a.train = 1;
     const int grid = std::min(B, net->num_cus);
-    if (launch_net(net, a, grid, st) != hipSuccess) { set_last_error("net launch failed"); return QLSD_E_DEVICE; }
+    if (launch_train(net, a, grid, st) != hipSuccess) { set_last_error("net launch failed"); return QLSD_E_DEVICE; }
     return QLSD_OK;
 }
 
