@@ -68,6 +68,7 @@ struct qlsd_code_s {
     int32_t *d_fault_msg;  // message layout of the large-graph BP kernel (null when not built)
     uint16_t *d_row_msg;
     int min_rw;
+    int rank;  // rank of H over GF(2) (m <= 256, where global OSD-CS needs it; else 0)
     // host copies of the CSR row pointers and the CSC layout, for launch planning
     std::vector<int32_t> h_row_ptr, h_col_ptr, h_col_edge;
     // message strides already chosen for (slots, LDS budget, threads): decoders of one code
@@ -195,6 +196,31 @@ static bool configure_overflow(qlsd_decoder d, int W, bool require) {
 
 const char *qlsd_last_error(void) { return g_err; }
 
+// Rank of H over GF(2) for m <= 256: its columns, a few detectors each, inserted one by one into an
+// echelon basis of 256-bit vectors until there are m pivots.
+static int column_rank(int m, int n, const int32_t *col_ptr, const int32_t *row_idx) {
+    uint64_t basis[256][4];
+    bool have[256] = {};
+    int rank = 0;
+    for (int j = 0; j < n && rank < m; j++) {
+        uint64_t v[4] = {0, 0, 0, 0};
+        for (int e = col_ptr[j]; e < col_ptr[j + 1]; e++) v[row_idx[e] >> 6] ^= 1ull << (row_idx[e] & 63);
+        for (int w = 0; w < 4; w++)
+            while (v[w]) {
+                const int r = 64 * w + __builtin_ctzll(v[w]);
+                if (!have[r]) {
+                    memcpy(basis[r], v, sizeof(v));
+                    have[r] = true;
+                    rank++;
+                    v[0] = v[1] = v[2] = v[3] = 0;
+                    break;
+                }
+                for (int x = 0; x < 4; x++) v[x] ^= basis[r][x];
+            }
+    }
+    return rank;
+}
+
 qlsd_status qlsd_code_create(int32_t m, int32_t n, int64_t nnz, const int32_t *row_ptr,
                              const int32_t *col_idx, qlsd_code *out) {
     g_err[0] = 0;
@@ -295,6 +321,7 @@ qlsd_status qlsd_code_create(int32_t m, int32_t n, int64_t nnz, const int32_t *r
         c->g.deep_cw = col_ptr[j + 1] - col_ptr[j];
     }
     c->min_rw = min_rw;
+    c->rank = m <= 256 ? column_rank(m, n, col_ptr.data(), row_idx.data()) : 0;
     try {
         c->h_row_ptr.assign(row_ptr, row_ptr + m + 1);
         c->h_col_ptr = col_ptr;
@@ -641,6 +668,7 @@ static hipError_t run_osd0(qlsd_decoder d, const Ws &w, const uint8_t *syn, cons
     a.ws = w.wide_ws;
     a.cs_order = cs_order;
     a.omega = d->d_omega;
+    a.rank = d->code->rank;
     const int grid = d->osd_W == kWideW ? w.wide_grid : 8 * d->num_cus;
     return launch_osd0(a, d->osd_W, grid, s);
 }

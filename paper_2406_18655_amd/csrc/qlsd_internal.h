@@ -157,6 +157,7 @@ struct OsdArgs {
     uint64_t *ws;              // W = kWideW: grid * 2 * W * W * 64 words of basis
     int cs_order;              // 0: OSD-0; w in [1, kOsdCsMaxOrder]: global OSD-CS of order w (W <= 4)
     const int64_t *omega;      // n integer weights (OSD-CS)
+    int rank;                  // rank of H (OSD-CS)
 };
 constexpr int kOsdMaxSort = 4096;  // OSD-0 sorts n <= 4096 keys in LDS
 constexpr int kOsdCsMaxOrder = 12;
@@ -168,8 +169,17 @@ struct OsdCsLds {
     int64_t *tw;      // kOsdCsMaxOrder
     int32_t *dep;     // n
 };
+// (the sort's keys make room for the basis's 64 W images of W words when the sweep starts)
+__host__ __device__ inline size_t osd_key_words(int W, int P, bool cs) {
+    const size_t images = cs && W <= 4 ? (size_t)64 * W * W : 0;
+    return images > (size_t)P ? images : (size_t)P;
+}
+// keys, pivot columns, correction bits; then the OSD-CS arrays
+__host__ __device__ inline size_t osd_head_bytes(int n, int W, int P, bool cs) {
+    return (osd_key_words(W, P, cs) * 8 + (size_t)64 * W * 4 + (size_t)((n + 31) / 32) * 4 + 15) & ~(size_t)15;
+}
 __host__ __device__ inline size_t osd0_wave_bytes_w(int n, int W, int P, bool cs) {
-    size_t b = ((size_t)P * 8 + (size_t)64 * W * 4 + (size_t)((n + 31) / 32) * 4 + 15) & ~(size_t)15;
+    size_t b = osd_head_bytes(n, W, P, cs);
     if (cs) b += (8 * ((size_t)64 * W + (size_t)kOsdCsMaxOrder * W + kOsdCsMaxOrder) + 4 * (size_t)n + 15) & ~(size_t)15;
     return b;
 }

@@ -187,6 +187,7 @@ struct Basis<W, false, false> {
     __device__ __forceinline__ uint64_t &C(int s, int w) { return CT[s][w]; }
     __device__ __forceinline__ uint64_t M(int s, int w) const { return Mrow[s][w]; }
     __device__ __forceinline__ uint64_t C(int s, int w) const { return CT[s][w]; }
+    __device__ __forceinline__ uint64_t unsolved(int s) const { return sp[s]; }
     // slice s of local rows (or of pivot rows) may be non-zero; the register code bounds its
     // loops at compile time instead (insert_column picks a tier from ns)
     __device__ __forceinline__ bool active(int) const { return true; }
@@ -216,6 +217,7 @@ struct Basis<W, true, InLds> {
     __device__ __forceinline__ auto &C(int s, int w) { return mem[((W + s) * W + w) * 64]; }
     __device__ __forceinline__ uint64_t M(int s, int w) const { return mem[(s * W + w) * 64]; }
     __device__ __forceinline__ uint64_t C(int s, int w) const { return mem[((W + s) * W + w) * 64]; }
+    __device__ __forceinline__ uint64_t unsolved(int s) const { return sp[s]; }
     __device__ __forceinline__ bool active(int s) const { return s < ns; }
     template <int NS = W>
     __device__ __forceinline__ uint64_t row_word(int rs, int w, int rl) const {
@@ -385,6 +387,154 @@ __device__ __forceinline__ bool insert_column(BB &B, const LsdLds &S, int col, i
     return true;
 }
 
+// The register basis of the LSD kernels and of global OSD (W <= 4): the Gauss-Jordan transform itself, by
+// columns.  Lane l holds, for local rows l, l + 64, ..., the image of that row's unit vector under all
+// eliminations so far (T(s, w): bits 64w .. 64w + 63 of row 64 s + l's image).  A new column has a handful
+// of local rows, so its reduction is the exclusive or of as many images, fetched with readlane into
+// scalar registers: a wave-uniform vector over the local rows.  Its bits outside the pivot rows give the
+// new pivot (the lowest one); if there are none the column is dependent and its bits are the pivots whose
+// columns combine to it.  A pivot at row r updates every image with bit r by one exclusive or per word,
+// and the reduced syndrome like an image: on a pivot row it is that column's bit of the solution.
+// Against Basis (per-row words and the combinations behind every pivot, both updated per pivot, with a
+// popcount parity and a ballot per slice to reduce a column) an insertion takes about a quarter of the
+// instructions and the basis half the registers: LSD of the shots BP 50 leaves of 65,536
+// [[144,12,12]] shots as a kernel of its own 348 -> 329 us, LSD-16 with its sweep 485 -> 380 us, hypergraph
+// product 432 x 900 606 -> 548 us, global OSD-CS-7 702 -> 313 us (with the sweep below).
+template <int W>
+struct ColBasis {
+    uint64_t T[W][W];
+    uint64_t piv[W];  // uniform: pivot local rows
+    uint64_t sp[W];   // uniform: reduced syndrome over local rows
+    int ns;           // uniform: slices 0..ns-1 of local rows are in use
+    static constexpr bool kInMem = false;
+    __device__ __forceinline__ void init(int lane) {
+#pragma unroll
+        for (int s = 0; s < W; s++) {
+#pragma unroll
+            for (int w = 0; w < W; w++) T[s][w] = s == w ? 1ull << lane : 0ull;
+            piv[s] = 0;
+        }
+    }
+    // adds the image of local row r (uniform, below 64 NS) to t
+    template <int NS>
+    __device__ __forceinline__ void fold(int r, uint64_t (&t)[W]) const {
+#pragma unroll
+        for (int s = 0; s < NS; s++)
+            if ((r >> 6) == s) {
+#pragma unroll
+                for (int w = 0; w < NS; w++) t[w] ^= readlane64(T[s][w], r & 63);
+            }
+    }
+    // t: the exclusive or of the images of the local rows in lanes base .. base + cw - 1 of lr_src (-1: no
+    // entry), all below 64 NS; uniform
+    template <int NS>
+    __device__ __forceinline__ void reduce(int lr_src, int base, int cw, uint64_t (&t)[W]) const {
+#pragma unroll
+        for (int w = 0; w < W; w++) t[w] = 0;
+        for (int u = 0; u < cw; u++) {
+            const int lr = __builtin_amdgcn_readlane(lr_src, base + u);
+            if (lr < 0 || lr >= 64 * NS) continue;
+            fold<NS>(lr, t);
+        }
+    }
+    // makes the reduced column t a pivot at its lowest row outside the pivots; returns that row, or -1 (a
+    // dependent column, the basis unchanged)
+    template <int NS>
+    __device__ __forceinline__ int add(const uint64_t (&t)[W]) {
+        int rs = -1;
+        uint64_t f = 0;
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+            const uint64_t g = t[s] & ~piv[s];
+            if (rs < 0 && g) {
+                rs = s;
+                f = g;
+            }
+        }
+        if (rs < 0) return -1;
+        const int rl = __builtin_ctzll(f);
+        uint64_t e[W];  // the rows the pivot is eliminated from
+#pragma unroll
+        for (int w = 0; w < NS; w++) e[w] = t[w] ^ (w == rs ? 1ull << rl : 0ull);
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+            uint64_t v = 0;
+#pragma unroll
+            for (int w = 0; w < NS; w++)
+                if (w == rs) v = T[s][w];
+            const int32_t mask = (int32_t)((v << (63 - rl)) >> 32) >> 31;  // all ones where the image has row r
+#pragma unroll
+            for (int w = 0; w < NS; w++) {
+                const uint32_t lo = (uint32_t)e[w] & (uint32_t)mask, hi = (uint32_t)(e[w] >> 32) & (uint32_t)mask;
+                T[s][w] ^= (uint64_t)hi << 32 | lo;
+            }
+        }
+        bool hit = false;
+#pragma unroll
+        for (int s = 0; s < NS; s++)
+            if (s == rs) {
+                hit = (sp[s] >> rl) & 1ull;
+                piv[s] = uniform64(piv[s] | 1ull << rl);
+            }
+        if (hit) {
+#pragma unroll
+            for (int w = 0; w < NS; w++) sp[w] = uniform64(sp[w] ^ e[w]);
+        }
+        return rs * 64 + rl;
+    }
+    // calls f with the tier of the slices in use: loops stop at 1, 2 or W slices at compile time
+    template <class F>
+    __device__ __forceinline__ auto tier(F &&f) const {
+        if constexpr (W == 4) {
+            return ns <= 1 ? f(std::integral_constant<int, 1>{})
+                   : ns <= 2 ? f(std::integral_constant<int, 2>{}) : f(std::integral_constant<int, 4>{});
+        } else if constexpr (W == 2) {
+            return ns <= 1 ? f(std::integral_constant<int, 1>{}) : f(std::integral_constant<int, 2>{});
+        } else {
+            return f(std::integral_constant<int, 1>{});
+        }
+    }
+    __device__ __forceinline__ uint64_t unsolved(int s) const { return sp[s] & ~piv[s]; }
+};
+
+template <int W>
+__device__ __forceinline__ bool insert_column(ColBasis<W> &B, const LsdLds &S, int col, int lane, int lr_src, int base,
+                                              int cw) {
+    const int row = B.tier([&](auto N) {
+        constexpr int NS = decltype(N)::value;
+        uint64_t t[W];
+        B.template reduce<NS>(lr_src, base, cw, t);
+        return B.template add<NS>(t);
+    });
+    if (row < 0) return false;
+    if (lane == 0) S.colAt[row] = col;
+    return true;
+}
+
+// Pivot rows whose columns combine to a dependent column; its local rows as for reduce.
+template <int W>
+__device__ __forceinline__ void combination(const ColBasis<W> &B, int lane, int lr_src, int cw, uint64_t (&z)[W]) {
+    B.tier([&](auto N) {
+        B.template reduce<decltype(N)::value>(lr_src, 0, cw, z);
+        return 0;
+    });
+#pragma unroll
+    for (int s = 0; s < W; s++) z[s] &= B.piv[s];
+}
+template <int W, bool InMem, bool InLds>
+__device__ __forceinline__ void combination(const Basis<W, InMem, InLds> &B, int lane, int lr_src, int cw, uint64_t (&z)[W]) {
+    uint32_t bf = 0;
+    for (int u = 0; u < cw; u++) {
+        const int lr = __builtin_amdgcn_readlane(lr_src, u);
+        if (lr >= 0 && lr < 64 * W && (lr & 63) == lane) bf |= 1u << (lr >> 6);
+    }
+    uint64_t a[W];
+#pragma unroll
+    for (int s = 0; s < W; s++) a[s] = ballot((bf >> s) & 1u) & B.piv[s];
+#pragma unroll
+    for (int s = 0; s < W; s++) z[s] = ballot(((B.piv[s] >> lane) & 1ull) && parity_C<W>(B, s, a));
+}
+
 __device__ __forceinline__ bool in_col(const uint32_t *incol, int j) { return (incol[j >> 5] >> (j & 31)) & 1u; }
 
 
@@ -394,16 +544,40 @@ __device__ __forceinline__ bool in_col(const uint32_t *incol, int j) { return (i
 // the pivot combination of column T_k (every T_k lies in the span of the pivots).  The cost is
 // the integer weight of the set columns; the strictly smallest cost wins, the smaller t on ties.
 // Patterns are spread over the lanes.
-// Integer weight of the pivot columns set in x (uniform; every lane computes the same sum).
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, off, 64);
+        const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)((uint64_t)v >> 32), off, 64);
+        v += (int64_t)((uint64_t)hi << 32 | lo);
+    }
+    return v;
+}
+// Integer weight of the pivot columns set in x (uniform): each lane weighs its rows.
 template <int W>
-__device__ __forceinline__ int64_t pivot_cost(const LsdLds &S, const uint64_t (&x)[W]) {
+__device__ __forceinline__ int64_t pivot_cost(const int64_t *wq, const uint64_t (&x)[W], int lane) {
+    int64_t v = 0;
+#pragma unroll
+    for (int s = 0; s < W; s++)
+        if ((x[s] >> lane) & 1ull) v += wq[s * 64 + lane];
+    return wave_sum_i64(v);
+}
+// Integer weight of the pivot columns set in each lane's own y; u (uniform) covers the rows any lane may
+// set.  All lanes walk the same rows, eight at a time, with broadcast reads of the weights: 64 candidates
+// cost about six instructions a row (a candidate at a time took a dependent LDS read per set bit).
+template <int W>
+__device__ __forceinline__ int64_t lane_cost(const int64_t *wq, const uint64_t (&y)[W], const uint64_t (&u)[W]) {
     int64_t cost = 0;
 #pragma unroll
     for (int s = 0; s < W; s++) {
-        uint64_t v = x[s];
-        while (v) {
-            cost += S.wq[s * 64 + __builtin_ctzll(v)];
-            v &= v - 1;
+        for (int b = 0; b < 64; b += 8) {
+            if (((u[s] >> b) & 0xffull) == 0) continue;
+            const int32_t bits = (int32_t)(uint32_t)(y[s] >> b);
+            int64_t w[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) w[k] = wq[s * 64 + b + k];
+#pragma unroll
+            for (int k = 0; k < 8; k++) cost += w[k] & (int64_t)((int32_t)(bits << (31 - k)) >> 31);
         }
     }
     return cost;
@@ -413,17 +587,11 @@ __device__ __forceinline__ int64_t pivot_cost(const LsdLds &S, const uint64_t (&
 template <int W, class G, class BB>
 __device__ __forceinline__ void column_combination(const LsdLds &S, const G &g, const BB &B, const uint64_t (&inC)[W],
                                                    int col, int lane, uint64_t (&z)[W]) {
-    constexpr int K = 64 * W;
-    uint32_t bf = 0;
-    for (int e = g.col_ptr(col); e < g.col_ptr(col + 1); e++) {
-        const int lr = S.loc[g.row_idx(e)];
-        if (lr >= 0 && lr < K && (lr & 63) == lane) bf |= 1u << (lr >> 6);
-    }
-    uint64_t a[W];
+    const int c0 = g.col_ptr(col), cw = __builtin_amdgcn_readfirstlane(g.col_ptr(col + 1) - c0);
+    const int lr = lane < cw ? S.loc[g.row_idx(c0 + lane)] : -1;
+    combination<W>(B, lane, lr, cw, z);
 #pragma unroll
-    for (int s = 0; s < W; s++) a[s] = ballot((bf >> s) & 1u) & B.piv[s];
-#pragma unroll
-    for (int s = 0; s < W; s++) z[s] = ballot(((B.piv[s] & inC[s]) >> lane) & 1ull && parity_C<W>(B, s, a));
+    for (int s = 0; s < W; s++) z[s] &= inC[s];
 }
 
 // Local OSD-CS (combination sweep) of one valid cluster c: candidates in the order zero pattern,
@@ -434,34 +602,54 @@ __device__ __forceinline__ void column_combination(const LsdLds &S, const G &g, 
 template <int W, int KNP, class G, class BB>
 __device__ void osd_cs_cluster(const LsdArgs &A, const LsdLds &S, const G &g, const BB &B, const uint64_t (&xc)[W],
                                const uint64_t (&inC)[W], int c, int nnp, int w, const float *llr, int lane) {
-    const int64_t cost0 = pivot_cost<W>(S, xc);
-    // singles: every dependent column of the cluster, best (cost, key)
+    const int64_t cost0 = pivot_cost<W>(S.wq, xc, lane);
+    // the rows a candidate may set: the cluster's pivots
+    uint64_t rows[W];
+#pragma unroll
+    for (int s = 0; s < W; s++) rows[s] = B.piv[s] & inC[s];
+    // singles: every dependent column of the cluster, best (cost, key); 64 list entries at a time, a
+    // column of the cluster to its entry's lane
     int64_t bs_cost = INT64_MAX;
     uint64_t bs_key = ~0ull;
-    for (int e = 0; e < nnp; e++) {
-        const int col = __builtin_amdgcn_readfirstlane(S.colNP[e]);
-        const int rr = S.loc[g.row_idx(g.col_ptr(col))];
-        if (__builtin_amdgcn_readfirstlane(S.croot[rr]) != c) continue;
-        uint64_t z[W], x[W];
-        column_combination<W>(S, g, B, inC, col, lane, z);
+    for (int e0 = 0; e0 < nnp; e0 += 64) {
+        const bool have = e0 + lane < nnp;
+        const int mine = have ? S.colNP[e0 + lane] : 0;
+        uint64_t members = ballot(have && S.croot[S.loc[g.row_idx(g.col_ptr(mine))]] == c);
+        const bool member = (members >> lane) & 1ull;
+        if (!members) continue;
+        uint64_t y[W];
 #pragma unroll
-        for (int s = 0; s < W; s++) x[s] = xc[s] ^ z[s];
-        const int64_t cost = pivot_cost<W>(S, x) + A.omega[col];
-        const uint32_t kj = (G::kInLds || A.keys_in_lds) ? S.keys[col] : ordered_key(llr[col]);
-        const uint64_t key = ((uint64_t)kj << 32) | (uint32_t)col;
-        if (cost < bs_cost || (cost == bs_cost && key < bs_key)) { bs_cost = cost; bs_key = key; }
+        for (int s = 0; s < W; s++) y[s] = xc[s];
+        while (members) {
+            const int l = __builtin_ctzll(members);
+            members &= members - 1;
+            uint64_t z[W];
+            column_combination<W>(S, g, B, inC, __builtin_amdgcn_readlane(mine, l), lane, z);
+            if (lane == l) {
+#pragma unroll
+                for (int s = 0; s < W; s++) y[s] ^= z[s];
+            }
+        }
+        const int64_t cost = lane_cost<W>(S.wq, y, rows) + (member ? A.omega[mine] : 0);
+        const uint32_t kj = member ? ((G::kInLds || A.keys_in_lds) ? S.keys[mine] : ordered_key(llr[mine])) : 0u;
+        // smallest cost, then smallest key (costs are far below 2^62)
+        const uint64_t ck = wave_min_u64(member ? (uint64_t)(cost + (1ll << 62)) : ~0ull);
+        const int64_t best = (int64_t)ck - (1ll << 62);
+        const uint64_t key = wave_min_u64(member && cost == best ? ((uint64_t)kj << 32) | (uint32_t)mine : ~0ull);
+        if (best < bs_cost || (best == bs_cost && key < bs_key)) { bs_cost = best; bs_key = key; }
     }
     // pairs among T_w, lexicographic index order
     const int npair = w * (w - 1) / 2;
     uint64_t bp = ~0ull;  // (cost + 2^50) << 12 | pair index, the smallest per lane
-    for (int p = lane; p < npair; p += 64) {
+    for (int p0 = 0; p0 < npair; p0 += 64) {
+        const int p = p0 + lane < npair ? p0 + lane : 0;
         int a = 0, rem = p;
         while (rem >= w - 1 - a) { rem -= w - 1 - a; a++; }
         const int b = a + 1 + rem;
         uint64_t x[W];
 #pragma unroll
         for (int s = 0; s < W; s++) x[s] = xc[s] ^ S.zk[a * W + s] ^ S.zk[b * W + s];
-        const int64_t cost = pivot_cost<W>(S, x) + S.tw[a] + S.tw[b];
+        const int64_t cost = lane_cost<W>(S.wq, x, rows) + S.tw[a] + S.tw[b];
         const uint64_t key = ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)p;
         bp = key < bp ? key : bp;
     }
@@ -519,11 +707,15 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
     wave_sync();
     const int nnp = npc < KNP ? npc : KNP;
     using Chosen = typename std::conditional<(KNP > 32 * 64), uint64_t, uint32_t>::type;
+#pragma unroll 1
+    for (int s0 = 0; s0 < W; s0++) {  // one copy of the body: the slice's roots are picked by compares
+        uint64_t left = 0;
 #pragma unroll
-    for (int s0 = 0; s0 < W; s0++) {
-        while (roots[s0]) {
-            const int c = s0 * 64 + __builtin_ctzll(roots[s0]);
-            roots[s0] &= roots[s0] - 1;
+        for (int s = 0; s < W; s++)
+            if (s == s0) left = roots[s];
+        while (left) {
+            const int c = s0 * 64 + __builtin_ctzll(left);
+            left &= left - 1;
             uint64_t inC[W];
 #pragma unroll
             for (int s = 0; s < W; s++) {
@@ -550,18 +742,11 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
                 for (int u = 0; u * 64 + lane < nnp; u++)
                     if (S.colNP[u * 64 + lane] == col) chosen |= Chosen(1) << u;
                 // z_w: pivot rows of this cluster whose combination reproduces column col
-                uint32_t bf = 0;
-                for (int e = g.col_ptr(col); e < g.col_ptr(col + 1); e++) {
-                    const int lr = S.loc[g.row_idx(e)];
-                    if (lr >= 0 && lr < K && (lr & 63) == lane) bf |= 1u << (lr >> 6);
-                }
-                uint64_t a[W];
+                uint64_t z[W];
+                column_combination<W>(S, g, B, inC, __builtin_amdgcn_readfirstlane(col), lane, z);
+                if (lane == 0) {
 #pragma unroll
-                for (int s = 0; s < W; s++) a[s] = ballot((bf >> s) & 1u) & B.piv[s];
-#pragma unroll
-                for (int s = 0; s < W; s++) {
-                    const uint64_t z = ballot(((B.piv[s] & inC[s]) >> lane) & 1ull && parity_C<W>(B, s, a));
-                    if (lane == 0) S.zk[w * W + s] = z;
+                    for (int s = 0; s < W; s++) S.zk[w * W + s] = z[s];
                 }
                 if (lane == 0) {
                     S.tsel[w] = col;
@@ -579,7 +764,11 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
             // search the 2^w patterns
             const int npat = 1 << w;
             uint64_t best = ~0ull;
-            for (int pt = lane; pt < npat; pt += 64) {
+            uint64_t rows[W];
+#pragma unroll
+            for (int s = 0; s < W; s++) rows[s] = B.piv[s] & inC[s];
+            for (int p0 = 0; p0 < npat; p0 += 64) {
+                const int pt = (p0 + lane) & (npat - 1);  // fewer than 64: some twice, with the same key
                 uint64_t x[W];
                 int64_t cost = 0;
 #pragma unroll
@@ -591,14 +780,7 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
                         for (int s = 0; s < W; s++) x[s] ^= S.zk[k * W + s];
                     }
                 }
-#pragma unroll
-                for (int s = 0; s < W; s++) {
-                    uint64_t v = x[s];
-                    while (v) {
-                        cost += S.wq[s * 64 + __builtin_ctzll(v)];
-                        v &= v - 1;
-                    }
-                }
+                cost += lane_cost<W>(S.wq, x, rows);
                 const uint64_t key = ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)pt;
                 best = key < best ? key : best;
             }
@@ -912,7 +1094,11 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
     const int nseed = nrows;
     if (lane == 0) S.ctl[0] = nrows;
 
-    Basis<W, WIDE, BLDS> B;
+    // the cluster-batched schedule reduces on Basis's rows
+    using BB = typename std::conditional<WIDE || CB, Basis<W, WIDE, BLDS>, ColBasis<W>>::type;
+    constexpr bool COLS = !WIDE && !CB;
+    BB B;
+    if constexpr (COLS) B.init(lane);
     if constexpr (WIDE) {
         // rows and pivots only ever occupy the first min(ceil(m/64), W) slices (a shot with more
         // rows has overflowed); the rest stays untouched
@@ -924,7 +1110,7 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
     B.ns = (nrows + 63) >> 6;
 #pragma unroll
     for (int s = 0; s < W; s++) {
-        if constexpr (!WIDE) {
+        if constexpr (!WIDE && CB) {
 #pragma unroll
             for (int w = 0; w < W; w++) { B.M(s, w) = 0; B.C(s, w) = 0; }
         }
@@ -1242,7 +1428,7 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
             const int r = s * 64 + lane;
             crv[s] = S.croot[r];
             stv[s] = S.state[r];
-            if (r < nrows && ((B.sp[s] >> lane) & 1ull)) vmark[crv[s]] = stamp;
+            if (r < nrows && ((B.unsolved(s) >> lane) & 1ull)) vmark[crv[s]] = stamp;
         }
         wave_sync();
         bool inv_mine = false;
@@ -1305,7 +1491,8 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
 #pragma unroll
     for (int s = 0; s < W; s++) {
         const int r = s * 64 + lane;
-        const bool seed = r < nseed && S.state[S.croot[r]] != kFrozen;
+        // (the column basis holds the solution on its pivot rows: every row of a cluster not frozen)
+        const bool seed = r < (COLS ? nrows : nseed) && S.state[S.croot[r < nrows ? r : 0]] != kFrozen;
         as[s] = ballot(seed) & B.piv[s];
     }
     int ncl = 0;
@@ -1315,7 +1502,8 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
         const int r = s * 64 + lane;
         const bool is_root = r < nrows && S.croot[r] == r;
         ncl += __popcll(ballot(is_root));
-        x0[s] = ballot(((B.piv[s] >> lane) & 1ull) && parity_C<W>(B, s, as));
+        if constexpr (COLS) x0[s] = B.sp[s] & B.piv[s] & as[s];
+        else x0[s] = ballot(((B.piv[s] >> lane) & 1ull) && parity_C<W>(B, s, as));
     }
     if (!MU || A.mu <= 0) {
 #pragma unroll

@@ -18,32 +18,109 @@
 // met first.  A column t of T changes the pivot part by z_t, the pivot columns whose combination
 // equals column t, read off the final basis.
 //
-// MI355X mapping: one wavefront per shot.  The shot's keys are sorted in LDS by a bitonic
-// network of wave-wide compare-exchange passes; the basis is the bit-sliced one of the LSD
-// kernels (lane l holds detector rows l, l + 64, ...), in registers for m <= 256 and in the
-// workgroup's slice of device memory for m <= 1024.
+// MI355X mapping: one wavefront per shot.  For m <= 256 the basis is the LSD kernels' column basis in
+// registers (ColBasis: a column of weight w costs w images read across the lanes, and a dependent
+// column's reduction is at once its combination of pivot columns); the columns' detectors are read 64
+// columns at a time, a column to a lane, and the sweep weighs 64 candidates at a time, a candidate to
+// a lane.  For m <= 1024 it is the wide LSD kernel's basis in the workgroup's slice of device memory.
 #include "qlsd_lsd_dev.h"
 
 namespace qlsd {
 
 namespace {
 
-// z: the pivot columns whose combination reproduces column col, as pivot rows (global basis:
-// local rows are detectors).
-template <int W, class BB>
-__device__ __forceinline__ void global_column_combination(const DevGraph &g, const BB &B, int col, int lane,
-                                                          uint64_t (&z)[W]) {
-    uint32_t bf = 0;
-    for (int e = g.col_ptr[col]; e < g.col_ptr[col + 1]; e++) {
-        const int r = g.row_idx[e];
-        if ((r & 63) == lane) bf |= 1u << (r >> 6);
+// Ascending sort of the n keys in LDS (padded to P, a power of two, with keys that sort last).  Few keys:
+// each lane ranks its own against all of them (broadcast reads, no exchanges; keys are distinct), which
+// avoids
+// the bitonic network's 36 dependent passes at 256 keys.
+constexpr int kRankSort = 256;
+template <int PER>
+__device__ __forceinline__ void rank_sort(uint64_t *keys, int n, int lane) {
+    uint64_t k[PER];
+    int rank[PER];
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+        k[q] = lane + 64 * q < n ? keys[lane + 64 * q] : ~0ull;
+        rank[q] = 0;
     }
-    uint64_t a[W];
+#pragma unroll 4
+    for (int j = 0; j < n; j++) {
+        const uint64_t v = keys[j];
 #pragma unroll
-    for (int s = 0; s < W; s++) a[s] = ballot((bf >> s) & 1u) & B.piv[s];
+        for (int q = 0; q < PER; q++) rank[q] += v < k[q] ? 1 : 0;
+    }
+    wave_sync();
 #pragma unroll
-    for (int s = 0; s < W; s++) z[s] = ballot(((B.piv[s] >> lane) & 1ull) && parity_C<W>(B, s, a));
+    for (int q = 0; q < PER; q++)
+        if (lane + 64 * q < n) keys[rank[q]] = k[q];
+    wave_sync();
 }
+__device__ __forceinline__ void sort_keys(uint64_t *keys, int n, int P, int lane) {
+    if (n <= 64) { rank_sort<1>(keys, n, lane); return; }
+    if (n <= 128) { rank_sort<2>(keys, n, lane); return; }
+    if (n <= 192) { rank_sort<3>(keys, n, lane); return; }
+    if (n <= kRankSort) { rank_sort<4>(keys, n, lane); return; }
+    for (int k = 2; k <= P; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int i = lane; i < P; i += 64) {
+                const int l = i ^ j;
+                if (l > i) {
+                    const uint64_t a = keys[i], b = keys[l];
+                    if ((a > b) == ((i & k) == 0)) { keys[i] = b; keys[l] = a; }
+                }
+            }
+            wave_sync();
+        }
+    }
+}
+
+// The detectors of 64 columns, a column to a lane: up to 16 of them, a byte each (m <= 256).
+struct ColumnRows {
+    uint32_t r[kMaxColWeight / 4];
+    int col, cw;
+    __device__ __forceinline__ void load(const DevGraph &g, bool have, int column) {
+        col = column;
+        cw = 0;
+#pragma unroll
+        for (int q = 0; q < kMaxColWeight / 4; q++) r[q] = 0u;
+        if (!have) return;
+        const int c0 = g.col_ptr[column];
+        cw = g.col_ptr[column + 1] - c0;
+#pragma unroll
+        for (int u = 0; u < kMaxColWeight; u++)
+            if (u < cw) r[u / 4] |= (uint32_t)g.row_idx[c0 + u] << (8 * (u & 3));
+    }
+    // lane l's column reduced against the basis (uniform)
+    template <int W>
+    __device__ __forceinline__ void reduce(const ColBasis<W> &B, int l, uint64_t (&t)[W]) const {
+        const int weight = __builtin_amdgcn_readlane(cw, l);
+#pragma unroll
+        for (int w = 0; w < W; w++) t[w] = 0;
+#pragma unroll
+        for (int q = 0; q < kMaxColWeight / 4; q++) {
+            if (4 * q >= weight) break;
+            const uint32_t rows = (uint32_t)__builtin_amdgcn_readlane((int)r[q], l);
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (4 * q + u >= weight) break;
+                B.template fold<W>((int)((rows >> (8 * u)) & 0xffu), t);
+            }
+        }
+    }
+    // every lane's own column reduced, from the images in LDS (row r's words at r * W)
+    template <int W>
+    __device__ __forceinline__ void reduce_own(const uint64_t *images, uint64_t (&t)[W]) const {
+#pragma unroll
+        for (int w = 0; w < W; w++) t[w] = 0;
+#pragma unroll
+        for (int u = 0; u < kMaxColWeight; u++) {
+            if (!ballot(u < cw)) break;
+            const uint64_t *im = images + ((r[u / 4] >> (8 * (u & 3))) & 0xffu) * W;
+#pragma unroll
+            for (int w = 0; w < W; w++) t[w] ^= u < cw ? im[w] : 0ull;
+        }
+    }
+};
 
 template <int W, bool WIDE, bool CS>
 __device__ void osd0_shot(const OsdArgs &A, uint64_t *keys, uint32_t *cbit, int32_t *colAt, const OsdCsLds &X,
@@ -86,58 +163,61 @@ __device__ void osd0_shot(const OsdArgs &A, uint64_t *keys, uint32_t *cbit, int3
     };
     if (ballot(nan)) { finish(QLSD_ST_LSD_RUN | QLSD_ST_BAD_LLR, 0); return; }
 
-    // ascending bitonic sort of the P keys
-    for (int k = 2; k <= P; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = lane; i < P; i += 64) {
-                const int l = i ^ j;
-                if (l > i) {
-                    const uint64_t a = keys[i], b = keys[l];
-                    if ((a > b) == ((i & k) == 0)) { keys[i] = b; keys[l] = a; }
-                }
-            }
-            wave_sync();
-        }
-    }
+    sort_keys(keys, n, P, lane);
 
-    Basis<W, WIDE> B;
+    using BB = typename std::conditional<WIDE, Basis<W, true>, ColBasis<W>>::type;
+    BB B;
+    bool any = false;
+#pragma unroll
+    for (int s = 0; s < W; s++) any |= sp0[s] != 0;
     if constexpr (WIDE) {
         B.mem = basis_mem + lane;
         const int msl = (m + 63) >> 6;
         for (int s = 0; s < msl; s++)
             for (int w = 0; w < msl; w++) { B.M(s, w) = 0; B.C(s, w) = 0; }
         B.ns = msl;
+#pragma unroll
+        for (int s = 0; s < W; s++) B.piv[s] = 0;
     } else {
-        B.ns = W;
+        B.init(lane);
+        B.ns = (m + 63) >> 6;
     }
-    bool any = false;
 #pragma unroll
-    for (int s = 0; s < W; s++) {
-        if constexpr (!WIDE) {
-#pragma unroll
-            for (int w = 0; w < W; w++) { B.M(s, w) = 0; B.C(s, w) = 0; }
-        }
-        B.piv[s] = 0;
-        B.sp[s] = sp0[s];
-        any |= sp0[s] != 0;
-    }
+    for (int s = 0; s < W; s++) B.sp[s] = sp0[s];
     // a zero syndrome: OSD-0's answer is zero; OSD-CS still sweeps (a column of negative weight,
     // a prior above 1/2, could make a nonzero solution lighter)
     if (!any && !CS) { finish(QLSD_ST_LSD_RUN, 0); return; }
     LsdLds S;
     S.colAt = colAt;
     S.wq = X.wq;
-    wave_sync();
-    int t = 0, nd = 0;
+    int t = 0, nd = 0, np = 0;
     bool spanned = false;
     // OSD-0 stops once the syndrome is in the span (later pivots would carry zeros); OSD-CS
-    // needs every dependent column, so it runs through all of them
-    while (t < n && (CS || !spanned)) {
-        const int col = __builtin_amdgcn_readfirstlane((int)(uint32_t)keys[t]);
-        const int c0 = __builtin_amdgcn_readfirstlane(A.g.col_ptr[col]);
-        const int cw = __builtin_amdgcn_readfirstlane(A.g.col_ptr[col + 1]) - c0;
-        const int lr = lane < cw ? A.g.row_idx[c0 + lane] : -1;
-        const bool piv = insert_column<W>(B, S, col, lane, lr, 0, cw);
+    // needs every dependent column: it stops once the pivots number rank(H), when the rest are
+    ColumnRows C;
+    while (t < n && (CS ? np < A.rank : !spanned)) {
+        bool piv;
+        int col;
+        if constexpr (WIDE) {
+            col = __builtin_amdgcn_readfirstlane((int)(uint32_t)keys[t]);
+            const int c0 = __builtin_amdgcn_readfirstlane(A.g.col_ptr[col]);
+            const int cw = __builtin_amdgcn_readfirstlane(A.g.col_ptr[col + 1]) - c0;
+            const int lr = lane < cw ? A.g.row_idx[c0 + lane] : -1;
+            piv = insert_column<W>(B, S, col, lane, lr, 0, cw);
+        } else {
+            const int l = t & 63;
+            if (l == 0) {
+                const bool have = t + lane < n;
+                C.load(A.g, have, have ? (int)(uint32_t)keys[t + lane] : 0);
+            }
+            col = __builtin_amdgcn_readlane(C.col, l);
+            uint64_t v[W];
+            C.reduce<W>(B, l, v);
+            const int row = B.template add<W>(v);
+            piv = row >= 0;
+            if (piv && lane == 0) colAt[row] = col;
+        }
+        np += piv ? 1 : 0;
         if constexpr (CS) {
             if (!piv) {
                 if (lane == 0) X.dep[nd] = col;
@@ -147,60 +227,83 @@ __device__ void osd0_shot(const OsdArgs &A, uint64_t *keys, uint32_t *cbit, int3
         t++;
         uint64_t rest = 0;
 #pragma unroll
-        for (int s = 0; s < W; s++) rest |= B.sp[s];
+        for (int s = 0; s < W; s++) rest |= B.unsolved(s);
         spanned = rest == 0;
+    }
+    if constexpr (CS) {
+        uint64_t rest = 0;  // (a matrix of rank 0 has reduced no column)
+#pragma unroll
+        for (int s = 0; s < W; s++) rest |= B.unsolved(s);
+        spanned = rest == 0;
+        for (int j = t + lane; j < n; j += 64) X.dep[nd + j - t] = (int)(uint32_t)keys[j];
+        nd += n - t;
+        t = n;  // every column counts as reduced
     }
     if (!spanned) { finish(QLSD_ST_LSD_RUN | QLSD_ST_UNSAT, t); return; }
     wave_sync();
-    // solution on the pivot columns: a pivot row's column is set iff its combination of the
-    // syndrome's pivot rows has odd parity
-    uint64_t as[W], x[W];
+    // solution on the pivot columns (the column basis's reduced syndrome; else a pivot row's column is
+    // set iff its combination of the syndrome's pivot rows has odd parity)
+    uint64_t x[W];
+    if constexpr (WIDE) {
+        uint64_t as[W];
 #pragma unroll
-    for (int s = 0; s < W; s++) as[s] = sp0[s] & B.piv[s];
+        for (int s = 0; s < W; s++) as[s] = sp0[s] & B.piv[s];
 #pragma unroll
-    for (int s = 0; s < W; s++) x[s] = ballot(((B.piv[s] >> lane) & 1ull) && parity_C<W>(B, s, as));
+        for (int s = 0; s < W; s++) x[s] = ballot(((B.piv[s] >> lane) & 1ull) && parity_C<W>(B, s, as));
+    } else {
+#pragma unroll
+        for (int s = 0; s < W; s++) x[s] = B.sp[s] & B.piv[s];
+    }
     if constexpr (CS) {
-        // combination sweep over T (dep[0 .. nd), ascending key)
+        // combination sweep over T (dep[0 .. nd), ascending key), 64 columns at a time, a column to a lane
+#pragma unroll
+        for (int s = 0; s < W; s++) X.wq[s * 64 + lane] = (B.piv[s] >> lane) & 1ull ? A.omega[colAt[s * 64 + lane]] : 0;
+        const int w = A.cs_order < nd ? A.cs_order : nd;
+        const int64_t cost0 = pivot_cost<W>(X.wq, x, lane);
+        // the images to LDS, over the keys (all columns are listed), for the lanes' own reductions
+        uint64_t *images = keys;
 #pragma unroll
         for (int s = 0; s < W; s++)
-            if ((B.piv[s] >> lane) & 1ull) X.wq[s * 64 + lane] = A.omega[colAt[s * 64 + lane]];
-        const int w = A.cs_order < nd ? A.cs_order : nd;
-        for (int a = 0; a < w; a++) {
-            const int col = __builtin_amdgcn_readfirstlane(X.dep[a]);
-            uint64_t z[W];
-            global_column_combination<W>(A.g, B, col, lane, z);
-            if (lane == 0) {
 #pragma unroll
-                for (int s = 0; s < W; s++) X.zk[a * W + s] = z[s];
-                X.tw[a] = A.omega[col];
+            for (int q = 0; q < W; q++) images[(s * 64 + lane) * W + q] = B.T[s][q];
+        wave_sync();
+        // singles: every column of T; the first of equal cost wins: smallest (cost + 2^50, index)
+        uint64_t bsk = ~0ull;
+        for (int e0 = 0; e0 < nd; e0 += 64) {
+            const bool have = e0 + lane < nd;
+            ColumnRows D;
+            D.load(A.g, have, have ? X.dep[e0 + lane] : 0);
+            uint64_t y[W], zl[W];  // a dependent column's reduction lies in the pivot rows
+            D.reduce_own<W>(images, zl);
+#pragma unroll
+            for (int s = 0; s < W; s++) y[s] = x[s] ^ zl[s];
+            const int64_t omega = have ? A.omega[D.col] : 0;
+            const int64_t cost = lane_cost<W>(X.wq, y, B.piv) + omega;
+            const uint64_t key = have ? ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)(e0 + lane) : ~0ull;
+            bsk = key < bsk ? key : bsk;
+            if (e0 == 0 && lane < w) {
+#pragma unroll
+                for (int s = 0; s < W; s++) X.zk[lane * W + s] = zl[s];
+                X.tw[lane] = omega;
             }
         }
         wave_sync();
-        const int64_t cost0 = pivot_cost<W>(S, x);
-        // singles: every column of T; the first of equal cost wins
-        int64_t bs_cost = INT64_MAX;
-        int bs = -1;
-        for (int e = 0; e < nd; e++) {
-            const int col = __builtin_amdgcn_readfirstlane(X.dep[e]);
-            uint64_t z[W], y[W];
-            global_column_combination<W>(A.g, B, col, lane, z);
-#pragma unroll
-            for (int s = 0; s < W; s++) y[s] = x[s] ^ z[s];
-            const int64_t cost = pivot_cost<W>(S, y) + A.omega[col];
-            if (cost < bs_cost) { bs_cost = cost; bs = e; }
-        }
+        bsk = wave_min_u64(bsk);
+        const int64_t bs_cost = bsk == ~0ull ? INT64_MAX : (int64_t)(bsk >> 12) - (1ll << 50);
+        const int bs = (int)(bsk & 4095ull);
         // pairs (a, b), a < b < w, lexicographic; spread over the lanes, the smallest
         // (cost, pair index) kept
         const int npair = w * (w - 1) / 2;
         uint64_t bp = ~0ull;
-        for (int p = lane; p < npair; p += 64) {
+        for (int p0 = 0; p0 < npair; p0 += 64) {
+            const int p = p0 + lane < npair ? p0 + lane : 0;
             int a = 0, rem = p;
             while (rem >= w - 1 - a) { rem -= w - 1 - a; a++; }
             const int b = a + 1 + rem;
             uint64_t y[W];
 #pragma unroll
             for (int s = 0; s < W; s++) y[s] = x[s] ^ X.zk[a * W + s] ^ X.zk[b * W + s];
-            const int64_t cost = pivot_cost<W>(S, y) + X.tw[a] + X.tw[b];
+            const int64_t cost = lane_cost<W>(X.wq, y, B.piv) + X.tw[a] + X.tw[b];
             const uint64_t key = ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)p;
             bp = key < bp ? key : bp;
         }
@@ -208,8 +311,9 @@ __device__ void osd0_shot(const OsdArgs &A, uint64_t *keys, uint32_t *cbit, int3
         const int64_t bp_cost = bp == ~0ull ? INT64_MAX : (int64_t)(bp >> 12) - (1ll << 50);
         if (bs_cost < cost0 && bs_cost <= bp_cost) {
             const int col = __builtin_amdgcn_readfirstlane(X.dep[bs]);
+            const int c0 = A.g.col_ptr[col], cw = __builtin_amdgcn_readfirstlane(A.g.col_ptr[col + 1] - c0);
             uint64_t z[W];
-            global_column_combination<W>(A.g, B, col, lane, z);
+            combination<W>(B, lane, lane < cw ? A.g.row_idx[c0 + lane] : -1, cw, z);
 #pragma unroll
             for (int s = 0; s < W; s++) x[s] ^= z[s];
             if (lane == 0) atomicOr(&cbit[col >> 5], 1u << (col & 31));
@@ -243,11 +347,11 @@ __global__ __launch_bounds__(WIDE ? 64 : 256) void osd0_kernel(OsdArgs A) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     unsigned char *base = smem + (size_t)wid * A.wave_bytes;
     uint64_t *keys = (uint64_t *)base;
-    int32_t *colAt = (int32_t *)(keys + A.P);
+    int32_t *colAt = (int32_t *)(keys + osd_key_words(W, A.P, CS));
     uint32_t *cbit = (uint32_t *)(colAt + 64 * W);
     OsdCsLds X;  // OSD-CS arrays after the OSD-0 block (8-byte aligned)
     {
-        unsigned char *q = base + osd0_wave_bytes_w(A.g.n, W, A.P, false);
+        unsigned char *q = base + osd_head_bytes(A.g.n, W, A.P, CS);
         X.wq = (int64_t *)q;
         X.zk = (uint64_t *)(X.wq + 64 * W);
         X.tw = (int64_t *)(X.zk + kOsdCsMaxOrder * W);
