@@ -603,6 +603,8 @@ static LsdArgs lsd_args(qlsd_decoder d, const Ws &w, const uint8_t *syn, const f
     a.omega = d->d_omega;
     a.wave_bytes = d->lsd_wave_bytes;
     a.cluster_batched = d->lsd_cb && d->lsd_W == 4;
+    // clusters held by the lanes (H and the keys in LDS: the arrays lie in the wavefront's block)
+    a.small = lsd_small_shape(a.g, d->lsd_W, d->params.lsd_order > 0) && d->lsd_graph_in_lds;
     return a;
 }
 

@@ -21,7 +21,7 @@
 #include <type_traits>
 
 #include "qlsd_internal.h"
-#include "qlsd_lsd_dev.h"
+#include "qlsd_lsd_small.h"
 
 namespace qlsd {
 
@@ -712,7 +712,9 @@ void bp_lds_kernel(BpArgs args, FuseArgs f) {
             const int h = __builtin_amdgcn_readfirstlane(r.y);
             if (shot < 0) break;  // no entry h, or it is left to the stand-alone launch (the call
                                   // that returned it has marked the previous shot done)
-            decode_shot<LSDW, false, decltype(gv), false, OVF>(f.lsd, S2, gv, shot, lane);  // LSD-0 only
+            // LSD-0 only
+            if (!f.lsd.small || !decode_small<LSDW>(f.lsd, lbase, gv, shot, lane))
+                decode_shot<LSDW, false, decltype(gv), false, OVF>(f.lsd, S2, gv, shot, lane);
             wave_sync();
             done_h = h;
             done_shot = shot;

@@ -79,7 +79,21 @@ struct LsdArgs {
     int *ovf_count;            //   appended here for the next overflow kernel (max_batch entries)
     qlsd_cluster_stats *cstats;  // B (nullable): per-shot statistics of the final clusters
     int cluster_batched;       // W = 4 kernel: reduce the round's columns batched across clusters
+    int small;                 // W <= 2 kernels: clusters held by the lanes (decode_small) where a shot allows it
 };
+
+// LSD on small codes with the clusters held by the lanes (qlsd_lsd_small.h).
+constexpr int kSmallFaults = 192, kSmallWords = kSmallFaults / 64;
+// LDS per wavefront (W words of checks)
+__host__ __device__ inline size_t lsd_small_bytes(int m, int n, int W) {
+    return (sizeof(uint64_t) * ((size_t)n * (W + kSmallWords) + (size_t)m * kSmallWords) + kSmallFaults / 8 +
+            2 * kSmallFaults + 64 + 7) & ~(size_t)7;
+}
+// LSD-0 in a kernel of 64 W local rows: every check has a row, the ranks fit three words (and a byte), and
+// every fault has a check, so a cluster's candidates are what its checks' entries hold.
+inline bool lsd_small_shape(const DevGraph &g, int W, bool with_mu) {
+    return !with_mu && W <= 2 && g.m <= 64 * W && g.n <= kSmallFaults && g.min_cw >= 1;
+}
 
 // BP with LSD folded in (plain decode with slot BP): a workgroup whose slots have drained turns
 // its wavefronts to LSD on shots that BP workgroups have published as unsolved.  lsd.list is the

@@ -22,7 +22,9 @@
 // solving are then per-lane AND/XOR/popcount plus a few ballots -- no cross-lane reductions.
 // Union-find over local rows lives in LDS (lock-free CAS hooking of the larger root under the
 // smaller one); candidate selection is a per-row scan plus an LDS 64-bit atomic min per root.
-#include "qlsd_lsd_dev.h"
+#include <algorithm>
+
+#include "qlsd_lsd_small.h"
 
 namespace qlsd {
 
@@ -66,7 +68,9 @@ void lsd_kernel(LsdArgs A) {
         if (item >= total) break;
         const int shot = A.list ? A.list[item] : item;
         if (A.skip_done && shot < 0) continue;
-        decode_shot<W, MU, GView<GL>, false, true, false, CB>(A, S, g, shot, lane);
+        bool done = false;
+        if constexpr (GL && W <= 2 && !MU) done = A.small && decode_small<W>(A, base, g, shot, lane);
+        if (!done) decode_shot<W, MU, GView<GL>, false, true, false, CB>(A, S, g, shot, lane);
         wave_sync();
     }
 }
@@ -227,7 +231,8 @@ hipError_t launch_compact(const uint8_t *flag, int B, int *list, int *count, hip
 
 size_t lsd_wave_bytes(const DevGraph &g, int W, bool keys_in_lds, bool with_mu) {
     size_t offs[kLsdLayoutEntries];
-    return lsd_layout(g.m, g.n, 64 * W, keys_in_lds, with_mu, offs);
+    const size_t b = lsd_layout(g.m, g.n, 64 * W, keys_in_lds, with_mu, offs);
+    return lsd_small_shape(g, W, with_mu) ? std::max(b, lsd_small_bytes(g.m, g.n, W)) : b;
 }
 
 size_t lsd_total_lds(const DevGraph &g, int W, bool keys_in_lds, bool graph_in_lds, bool with_mu) {

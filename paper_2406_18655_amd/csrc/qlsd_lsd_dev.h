@@ -415,6 +415,12 @@ struct ColBasis {
             piv[s] = 0;
         }
     }
+    // adds the image of local row 64 s + l (s a constant, l uniform) to t
+    template <int NS>
+    __device__ __forceinline__ void fold_slice(int s, int l, uint64_t (&t)[W]) const {
+#pragma unroll
+        for (int w = 0; w < NS; w++) t[w] ^= readlane64(T[s][w], l);
+    }
     // adds the image of local row r (uniform, below 64 NS) to t
     template <int NS>
     __device__ __forceinline__ void fold(int r, uint64_t (&t)[W]) const {

@@ -1,0 +1,108 @@
+"""LSD and global OSD at the edges of their shapes: numbers of faults and of checks around the
+64-bit words of the bases and fault sets, more flipped checks than a wavefront has lanes, dependent
+checks (syndromes outside the image), ties, NaN and empty syndromes.  Every result is a whole
+number and equals the oracle's."""
+import numpy as np
+import pytest
+
+from paper_2406_18655_amd import binding
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.lib()
+
+
+def _graph(m, n, seed):
+    """Columns of weight 1 to 6; the last check repeats the first, the two before it share their faults."""
+    rng = np.random.default_rng(seed)
+    H = np.zeros((m, n), dtype=np.uint8)
+    for j in range(n):
+        H[rng.choice(m - 3, size=min(m - 3, int(rng.choice([1, 2, 3, 4, 6], p=[.05, .25, .45, .2, .05]))),
+                     replace=False), j] = 1
+    for i in np.nonzero(H[:m - 3].sum(1) < 2)[0]:
+        H[i, rng.choice(np.nonzero(H[i] == 0)[0], size=2, replace=False)] = 1
+    H[m - 3, rng.choice(n, size=3, replace=False)] = 1
+    H[m - 2] = H[m - 3]
+    H[m - 1] = H[0]
+    return H
+
+
+def _shots(H, seed, dense):
+    """Sparse and dense errors, syndromes outside the image, soft information with and without ties."""
+    rng = np.random.default_rng(seed)
+    m, n = H.shape
+    rates = np.repeat([0.01, 0.03, 0.1, 0.3], 16)
+    E = (rng.random((len(rates), n)) < rates[:, None]).astype(np.int64)
+    S = (E @ H.T % 2).astype(np.uint8)
+    off = S[::4].copy()
+    off[np.arange(len(off)), rng.integers(m, size=len(off))] ^= 1
+    S = np.concatenate([S, off, np.zeros((2, m), np.uint8), np.ones((2, m), np.uint8),
+                        (rng.random((dense, m)) < 0.5).astype(np.uint8)])
+    L = (rng.normal(2.0, 2.0, size=(len(S), n))).astype(np.float32)
+    L[::3] = np.rint(L[::3] / 2)
+    L[1::9, ::4] = -0.0
+    return np.ascontiguousarray(S), np.ascontiguousarray(L)
+
+
+@pytest.mark.parametrize("m,n", [(8, 16), (24, 63), (63, 64), (64, 65), (65, 128), (64, 192), (100, 129),
+                                 (127, 191), (128, 192), (128, 193), (129, 192)])
+def test_lsd_of_small_graphs(oracle_mod, m, n):
+    print(f"case lsd_shapes lsd {m}x{n}", flush=True)
+    H = _graph(m, n, seed=m + n)
+    S, L = _shots(H, seed=m * n, dense=16)
+    bc = binding.Code.from_dense(H)
+    dec = binding.Decoder(bc, np.full(n, 0.02), len(S), max_iter=5)
+    L[5, n - 1] = np.nan
+    corr, info, st = dec.lsd_stats(torch.from_numpy(S).cuda(), torch.from_numpy(L).cuda())
+    plain, pinfo = dec.lsd(torch.from_numpy(S).cuda(), torch.from_numpy(L).cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(plain, corr) and torch.equal(pinfo, info)
+    c, st, inf = corr.cpu().numpy(), st.cpu().numpy(), binding.parse_info(info)
+    oc = oracle_mod.Code.from_dense(H)
+    assert inf["status"][5] & binding.ST_BAD_LLR and not c[5].any()
+    unsat = 0
+    for b in range(len(S)):
+        if b == 5:
+            continue
+        want, ost, stats = oracle_mod.lsd(oc, S[b], L[b].astype(np.float64))
+        assert not inf["status"][b] & (binding.ST_OVERFLOW | binding.ST_BAD_LLR), b
+        assert (c[b] == want).all(), b
+        assert bool(inf["status"][b] & binding.ST_UNSAT) == bool(ost & oracle_mod.ST_UNSAT), b
+        assert (inf["n_clusters"][b], inf["max_cluster_cols"][b]) == tuple(stats[:2]), b
+        # the oracle also counts a last round in which the clusters only find no fault left
+        assert stats[2] - inf["rounds"][b] in ((0, 1) if ost & oracle_mod.ST_UNSAT else (0,)), b
+        assert tuple(st[b]) == (stats[0], stats[1], stats[3], stats[6]), b
+        unsat += bool(ost & oracle_mod.ST_UNSAT)
+    assert unsat
+
+
+@pytest.mark.parametrize("m,n", [(8, 16), (64, 64), (64, 65), (65, 128), (128, 129), (96, 192), (129, 193),
+                                 (192, 256), (193, 257), (255, 300)])
+def test_osd_of_every_word_count(oracle_mod, m, n):
+    print(f"case lsd_shapes osd {m}x{n}", flush=True)
+    H = _graph(m, n, seed=m + 2 * n)
+    S, L = _shots(H, seed=m * n + 1, dense=4)
+    bc = binding.Code.from_dense(H)
+    priors = np.random.default_rng(3).uniform(0.005, 0.1, size=n)
+    dec = binding.Decoder(bc, priors, len(S), max_iter=5)
+    s, l = torch.from_numpy(S).cuda(), torch.from_numpy(L).cuda()
+    c0, i0 = dec.osd0(s, l)
+    order = 7
+    cs, ics = dec.osd_cs(s, l, order)
+    torch.cuda.synchronize()
+    c0, cs = c0.cpu().numpy(), cs.cpu().numpy()
+    st0, st1 = binding.parse_info(i0)["status"], binding.parse_info(ics)["status"]
+    oc = oracle_mod.Code.from_dense(H)
+    om = oracle_mod.omega_from_llr(oracle_mod.llr_from_priors(priors))
+    for b in range(len(S)):
+        L64 = L[b].astype(np.float64)
+        want, ost = oracle_mod.osd0(oc, S[b], L64)
+        assert (c0[b] == want).all() and bool(st0[b] & binding.ST_UNSAT) == bool(ost & oracle_mod.ST_UNSAT), b
+        want, ost = oracle_mod.osd_cs(oc, S[b], L64, order, om)
+        assert (cs[b] == want).all() and bool(st1[b] & binding.ST_UNSAT) == bool(ost & oracle_mod.ST_UNSAT), b
