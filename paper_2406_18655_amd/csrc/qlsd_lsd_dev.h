@@ -44,6 +44,28 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
     return v;
 }
 
+// Smallest of 64 values, by DPP within the rows of 16 lanes and then across them; uniform.
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+    auto step = [&](auto ctrl) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, decltype(ctrl)::value, 0xf, 0xf, false);
+        v = o < v ? o : v;
+    };
+    step(std::integral_constant<int, 0x111>{});  // row_shr 1, 2, 4, 8
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{});  // row_bcast 15, 31
+    step(std::integral_constant<int, 0x143>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// Smallest of 64 keys, uniform: the upper halves, then the lower halves of the lanes that hold it (about
+// 25 vector instructions; wave_min_u64's twelve shuffles go through LDS one after the other).
+__device__ __forceinline__ uint64_t wave_min_key(uint64_t v) {
+    const uint32_t hi = wave_min_u32((uint32_t)(v >> 32));
+    const uint32_t lo = wave_min_u32((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0xffffffffu);
+    return (uint64_t)hi << 32 | lo;
+}
+
 // Order-preserving map of a float32 LLR to uint32 (-0 treated as +0).
 __device__ __forceinline__ uint32_t ordered_key(float x) {
     uint32_t u = __float_as_uint(x);
@@ -97,6 +119,7 @@ struct LsdLds {
 // rows that may cache a column are its own detectors, all local rows by the time it is taken, so
 // taking a column marks exactly those rows kStale and the selection never tests the cached column.
 constexpr uint64_t kStale = ~0ull - 1ull;
+constexpr int kAhead = 4;  // edges a lane reads ahead of a lone round's insertion
 
 __host__ __device__ inline size_t align8(size_t x) { return (x + 7) & ~size_t(7); }
 
@@ -764,7 +787,11 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
 #pragma unroll
             for (int s = 0; s < W; s++) xc[s] = x0[s] & inC[s];
             if (A.cs_order > 0) {
-                osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane);
+                if constexpr (!BB::kInMem) {
+                    [[clang::always_inline]] osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane);
+                } else {
+                    osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane);
+                }
                 continue;
             }
             // search the 2^w patterns
@@ -1128,9 +1155,178 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
 
     // LSD-0 rounds grow the invalid clusters until none is left; LSD-mu then runs mu more
     // rounds in which every cluster that is not frozen grows (Appendix D).
+    // smallest candidate key among the edges e0 .. e1 - 1 of a row
+    auto scan_row = [&](int e0, int e1) -> uint64_t {
+                                uint64_t best = ~0ull;
+                                // kScan entries per pass, every load issued before any is used (entries
+                                // past the row's end re-read its last one and are masked out), so a row of
+                                // weight <= kScan costs two dependent rounds of loads (6 fits the small
+                                // codes' rows without masked slots; the large graphs' rows are longer)
+                                constexpr int kScan = W <= 2 ? 6 : 8;
+                                for (int eb = e0; eb < e1; eb += kScan) {
+                                    int jj[kScan];
+#pragma unroll
+                                    for (int u = 0; u < kScan; u++) jj[u] = g.col_idx(min(eb + u, e1 - 1));
+                                    uint32_t kk[kScan], ic[kScan];
+#pragma unroll
+                                    for (int u = 0; u < kScan; u++) {
+                                        kk[u] = (G::kInLds || A.keys_in_lds) ? S.keys[jj[u]] : ordered_key(llr[jj[u]]);
+                                        ic[u] = S.incol[jj[u] >> 5];
+                                    }
+#pragma unroll
+                                    for (int u = 0; u < kScan; u++) {
+                                        const bool ok = eb + u < e1 && !((ic[u] >> (jj[u] & 31)) & 1u);
+                                        const uint64_t key = ok ? (((uint64_t)kk[u] << 32) | (uint32_t)jj[u]) : ~0ull;
+                                        best = key < best ? key : best;
+                                    }
+                                }
+        return best;
+    };
     bool grow_all = false;
     int mu_left = 0;
     int npc = 0;  // dependent columns recorded in colNP
+    constexpr bool LONE = !WIDE && !CB;
+    // Rounds with one invalid cluster, until it is valid or has no candidate left (false: the shot outgrew
+    // the basis).  They are most rounds of the long shots, which set the time of a batch, and are bound by
+    // their chain of dependent accesses and by instruction issue of the one wavefront.  So the roots of
+    // this lane's rows stay in registers, the pick is a reduction across lanes instead of an atomic and a
+    // list, there are no claims to settle (the picking cluster takes every new detector) and no stamps for
+    // validity, and the rows of the new column look for their next candidate while it is inserted, several
+    // lanes a row.  A round of about 9,000 cycles takes about 5,000: hypergraph product 432 x 900, 2048
+    // shots at 3%, kernel alone 548 -> 318 us; windows of a 12-round memory 300 -> 170 us; LSD-16 with its
+    // sweep on [[144,12,12]] 380 -> 301 us; 936 x 8800 detector model, 37 shots, LSD-10 (graph in global
+    // memory) 410 -> 396 us.
+    auto lone_rounds = [&](int root, int (&rows_root)[W]) -> bool {
+        const int cw_log = g.max_cw <= 1 ? 0 : 32 - __builtin_clz((unsigned)(g.max_cw - 1));
+        const int u = lane & ((1 << cw_log) - 1), step = 64 >> cw_log;
+        for (;;) {
+            uint64_t best = ~0ull;
+#pragma unroll
+            for (int s = 0; s < W; s++) {
+                if (s * 64 >= nrows) break;
+                const int r = s * 64 + lane;
+                uint64_t k = S.cand[r];
+                const bool mine = r < nrows && rows_root[s] == root;
+                // (only rows that a round of several clusters marked, and a merge brought in since)
+                if (mine && k == kStale) {
+                    const int d = S.rowOf[r];
+                    k = scan_row(g.row_ptr(d), g.row_ptr(d + 1));
+                    S.cand[r] = k;
+                }
+                best = mine && k < best ? k : best;
+            }
+            const uint64_t pick = wave_min_key(best);
+            if (pick == ~0ull) {
+                if (lane == 0) S.state[root] = kFrozen;
+                status |= QLSD_ST_UNSAT;
+                wave_sync();
+                return true;
+            }
+            // Entry u of the column on the lanes u + 2^cw_log k, which share the scan of its row; lanes below
+            // 2^cw_log add the detectors that are new.
+            const int col = (int)(uint32_t)pick;
+            const int c0 = g.col_ptr(col), cw = g.col_ptr(col + 1) - c0;
+            const bool has = u < cw;
+            const int d = g.row_idx(has ? c0 + u : c0);
+            int lr = S.loc[d];
+            const int e0 = g.row_ptr(d) + (lane >> cw_log), e1 = has ? g.row_ptr(d + 1) : 0;
+            int jn[kAhead];
+            auto edges = [&](int e) {
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) {
+                    jn[k] = -1;
+                    if (e + k * step < e1) jn[k] = g.col_idx(e + k * step);
+                }
+            };
+            edges(e0);
+            const int oc = lr >= 0 ? S.croot[lr] : root;
+            const bool add = has && lr < 0 && lane < (1 << cw_log);
+            const uint64_t bal = ballot(add), meet = ballot(has && oc != root);
+            const int idx = nrows + __popcll(bal & ((1ull << u) - 1ull));
+            const int nrows_new = nrows + __popcll(bal);
+            if (nrows_new > K) return false;
+            // the clusters it meets join under the smallest root
+            if (meet) {
+                const int was = root;
+                bool mine[W];
+#pragma unroll
+                for (int s = 0; s < W; s++) mine[s] = rows_root[s] == was;
+                for (uint64_t o = meet; o;) {
+                    const int c = __builtin_amdgcn_readlane(oc, __builtin_ctzll(o));
+                    root = c < root ? c : root;
+#pragma unroll
+                    for (int s = 0; s < W; s++) mine[s] |= rows_root[s] == c;
+                    o &= ~ballot(oc == c);
+                }
+#pragma unroll
+                for (int s = 0; s < W; s++)
+                    if (mine[s] && s * 64 + lane < nrows) {
+                        rows_root[s] = root;
+                        S.croot[s * 64 + lane] = root;
+                    }
+            }
+            if (add) {
+                S.rowOf[idx] = d;
+                S.croot[idx] = root;
+                S.state[idx] = kValid;
+                S.loc[d] = idx;
+            }
+            if (has && lr < 0) lr = idx;
+            if (has) S.cand[lr] = ~0ull;
+            if (lane == 0) atomicOr(&S.incol[col >> 5], 1u << (col & 31));
+#pragma unroll
+            for (int s = 0; s < W; s++) {
+                const int r = s * 64 + lane;
+                if (r >= nrows && r < nrows_new) rows_root[s] = root;
+            }
+            nrows = nrows_new;
+            B.ns = (nrows + 63) >> 6;
+            uint32_t kk[kAhead], ic[kAhead];
+            auto fetch = [&]() {
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) {
+                    const int j = jn[k] < 0 ? col : jn[k];
+                    kk[k] = (G::kInLds || A.keys_in_lds) ? S.keys[j] : __float_as_uint(llr[j]);
+                    ic[k] = S.incol[j >> 5];
+                }
+            };
+            auto look = [&]() {
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) {
+                    const uint32_t v = (G::kInLds || A.keys_in_lds) ? kk[k] : ordered_key(__uint_as_float(kk[k]));
+                    const bool ok = jn[k] >= 0 && !((ic[k] >> (jn[k] & 31)) & 1u);
+                    const uint64_t key = ok ? (((uint64_t)v << 32) | (uint32_t)jn[k]) : ~0ull;
+                    best = key < best ? key : best;
+                }
+            };
+            fetch();
+            const bool pivot = insert_column<W>(B, S, col, lane, has ? lr : -1, 0, cw);
+            if (MU && !pivot && A.mu > 0) {
+                if (lane == 0 && npc < KNP) S.colNP[npc] = col;
+                npc++;
+            }
+            // the rows of the column look for their next candidate, read while the column was inserted
+            best = ~0ull;
+            look();
+            for (int e = e0 + kAhead * step; ballot(e < e1); e += kAhead * step) {
+                edges(e);
+                fetch();
+                look();
+            }
+            if (best != ~0ull) atomicMin((unsigned long long *)&S.cand[lr], (unsigned long long)best);
+            uint64_t bad = 0;
+#pragma unroll
+            for (int s = 0; s < W; s++)
+                bad |= ballot(s * 64 + lane < nrows && rows_root[s] == root) & B.unsolved(s);
+            wave_sync();
+            rounds++;
+            if (!bad) {
+                if (lane == 0) { S.state[root] = kValid; S.ctl[0] = nrows; }
+                wave_sync();
+                return true;
+            }
+        }
+    };
     for (;;) {
         // (1) selection: per growing root, the candidate of smallest key (round-start state);
         // every entry of sel is ~0 here
@@ -1159,34 +1355,12 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
             {
                 {
                     if (grow && best == kStale) {
-                        best = ~0ull;
                         if constexpr (!G::kInLds) {
                             const int d = S.rowOf[r];
                             e0 = g.row_ptr(d);
                             e1 = g.row_ptr(d + 1);
                         }
-                        // kScan entries per pass, every load issued before any is used (entries
-                        // past the row's end re-read its last one and are masked out), so a row of
-                        // weight <= kScan costs two dependent rounds of loads (6 fits the small
-                        // codes' rows without masked slots; the large graphs' rows are longer)
-                        constexpr int kScan = W <= 2 ? 6 : 8;
-                        for (int eb = e0; eb < e1; eb += kScan) {
-                            int jj[kScan];
-#pragma unroll
-                            for (int u = 0; u < kScan; u++) jj[u] = g.col_idx(min(eb + u, e1 - 1));
-                            uint32_t kk[kScan], ic[kScan];
-#pragma unroll
-                            for (int u = 0; u < kScan; u++) {
-                                kk[u] = (G::kInLds || A.keys_in_lds) ? S.keys[jj[u]] : ordered_key(llr[jj[u]]);
-                                ic[u] = S.incol[jj[u] >> 5];
-                            }
-#pragma unroll
-                            for (int u = 0; u < kScan; u++) {
-                                const bool ok = eb + u < e1 && !((ic[u] >> (jj[u] & 31)) & 1u);
-                                const uint64_t key = ok ? (((uint64_t)kk[u] << 32) | (uint32_t)jj[u]) : ~0ull;
-                                best = key < best ? key : best;
-                            }
-                        }
+                        best = scan_row(e0, e1);
                         S.cand[r] = best;
                     }
                     if (grow && best != ~0ull) atomicMin((unsigned long long *)&S.sel[c], (unsigned long long)best);
@@ -1437,22 +1611,32 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
             if (r < nrows && ((B.unsolved(s) >> lane) & 1ull)) vmark[crv[s]] = stamp;
         }
         wave_sync();
-        bool inv_mine = false;
+        uint64_t any_inv = 0;
+        int ninv = 0, inv_root = 0;
 #pragma unroll
         for (int s = 0; s < W; s++) {
             const int r = s * 64 + lane;
+            bool inv = false;
             if (r < nrows && crv[s] == r && stv[s] != kFrozen) {
-                const bool inv = vmark[r] == stamp;
+                inv = vmark[r] == stamp;
                 S.state[r] = inv ? kInvalid : kValid;
-                inv_mine |= inv;
             }
+            const uint64_t bal = ballot(inv);
+            any_inv |= bal;
+            ninv += __popcll(bal);
+            if (bal) inv_root = s * 64 + __builtin_ctzll(bal);
         }
-        const bool any_inv = ballot(inv_mine) != 0ull;
         wave_sync();
         rounds++;
         if (MU && grow_all) {
             if (--mu_left == 0) break;
             continue;
+        }
+        if constexpr (LONE) {
+            if (ninv == 1) {
+                if (!lone_rounds(inv_root, crv)) { overflow(status); return; }
+                any_inv = 0;
+            }
         }
         if (!any_inv) {
             if (!MU || A.mu <= 0) break;
@@ -1524,7 +1708,12 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
         finish(status, ncl, max_cluster_cols(ncl));
         return;
     }
-    if constexpr (MU) osd_e_clusters<W, KNP>(A, S, g, B, x0, nrows, npc, llr, lane);
+    // (a call would pass the register basis through memory)
+    if constexpr (MU && !BB::kInMem) {
+        [[clang::always_inline]] osd_e_clusters<W, KNP>(A, S, g, B, x0, nrows, npc, llr, lane);
+    } else if constexpr (MU) {
+        osd_e_clusters<W, KNP>(A, S, g, B, x0, nrows, npc, llr, lane);
+    }
     write_row();
     finish(status, ncl, max_cluster_cols(ncl));
 }

@@ -106,3 +106,55 @@ def test_osd_of_every_word_count(oracle_mod, m, n):
         assert (c0[b] == want).all() and bool(st0[b] & binding.ST_UNSAT) == bool(ost & oracle_mod.ST_UNSAT), b
         want, ost = oracle_mod.osd_cs(oc, S[b], L64, order, om)
         assert (cs[b] == want).all() and bool(st1[b] & binding.ST_UNSAT) == bool(ost & oracle_mod.ST_UNSAT), b
+
+
+def _heavy_graph(m, n, heavy, seed):
+    """Columns of weight 1 or 2 and, every ninth, of weight `heavy`; rows of weight 2 to 32."""
+    rng = np.random.default_rng(seed)
+    H = np.zeros((m, n), dtype=np.uint8)
+    load = np.zeros(m, dtype=int)
+    for j in range(n):
+        room = np.nonzero(load < 32)[0]
+        w = min(len(room), heavy if j % 9 == 0 else int(rng.integers(1, 3)))
+        rows = rng.choice(room, size=w, replace=False)
+        H[rows, j] = 1
+        load[rows] += 1
+    for i in np.nonzero(load < 2)[0]:
+        H[i, rng.choice(np.nonzero(H[i] == 0)[0], size=2, replace=False)] = 1
+    return H
+
+
+# lone growing clusters: columns of up to 1, 2, 8 and 16 checks (the lanes that share a row's edges), rows of
+# more edges than are read ahead, keys outside LDS (more than 4096 faults), rounds of all clusters after them
+@pytest.mark.parametrize("m,n,heavy,mu", [(90, 200, 1, 0), (150, 400, 2, 0), (140, 600, 7, 0), (130, 400, 15, 0),
+                                          (130, 400, 16, 3), (250, 4400, 3, 0), (250, 4400, 4, 2), (130, 200, 3, 5)])
+def test_lsd_of_lone_clusters(oracle_mod, m, n, heavy, mu):
+    print(f"case lsd_shapes lone {m}x{n} weight {heavy} mu {mu}", flush=True)
+    H = _heavy_graph(m, n, heavy, seed=m + n + heavy)
+    rng = np.random.default_rng(m * n)
+    # a few flipped checks, soft information that leads the growth astray: many rounds of few clusters
+    E = (rng.random((48, n)) < (np.arange(48) % 6 + 1)[:, None] / (2.0 * n)).astype(np.int64)
+    S = np.ascontiguousarray((E @ H.T % 2).astype(np.uint8))
+    S[::5, rng.integers(m)] ^= 1
+    L = rng.normal(2.0, 2.0, size=(48, n)).astype(np.float32)
+    L[::4] = np.rint(L[::4] / 2)
+    L = np.ascontiguousarray(L + 6.0 * E.astype(np.float32))
+    bc = binding.Code.from_dense(H)
+    priors = np.full(n, 0.02)
+    dec = binding.Decoder(bc, priors, 48, max_iter=5, lsd_order=mu)
+    corr, info, st = dec.lsd_stats(torch.from_numpy(S).cuda(), torch.from_numpy(L).cuda())
+    torch.cuda.synchronize()
+    c, st, inf = corr.cpu().numpy(), st.cpu().numpy(), binding.parse_info(info)
+    oc = oracle_mod.Code.from_dense(H)
+    om = oracle_mod.omega_from_llr(oracle_mod.llr_from_priors(priors))
+    most = 0
+    for b in range(48):
+        want, ost, stats = oracle_mod.lsd(oc, S[b], L[b].astype(np.float64), mu=mu, omega=om)
+        assert not inf["status"][b] & (binding.ST_OVERFLOW | binding.ST_BAD_LLR), b
+        assert (c[b] == want).all(), b
+        assert bool(inf["status"][b] & binding.ST_UNSAT) == bool(ost & oracle_mod.ST_UNSAT), b
+        assert tuple(st[b]) == (stats[0], stats[1], stats[3], stats[6]), b
+        if not ost & oracle_mod.ST_UNSAT:
+            assert inf["rounds"][b] == stats[2], b
+        most = max(most, int(inf["rounds"][b]))
+    print(f"  rounds up to {most}")
