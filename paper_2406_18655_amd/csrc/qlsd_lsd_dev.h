@@ -33,17 +33,6 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t lo = __shfl_xor((int)(uint32_t)v, off, 64);
-        const uint32_t hi = __shfl_xor((int)(uint32_t)(v >> 32), off, 64);
-        const uint64_t o = ((uint64_t)hi << 32) | lo;
-        v = o < v ? o : v;
-    }
-    return v;
-}
-
 // Smallest of 64 values, by DPP within the rows of 16 lanes and then across them; uniform.
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     auto step = [&](auto ctrl) {
@@ -59,7 +48,7 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 // Smallest of 64 keys, uniform: the upper halves, then the lower halves of the lanes that hold it (about
-// 25 vector instructions; wave_min_u64's twelve shuffles go through LDS one after the other).
+// 25 vector instructions; shuffles of 64-bit keys go through LDS twelve times, one after the other).
 __device__ __forceinline__ uint64_t wave_min_key(uint64_t v) {
     const uint32_t hi = wave_min_u32((uint32_t)(v >> 32));
     const uint32_t lo = wave_min_u32((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0xffffffffu);
@@ -542,19 +531,21 @@ __device__ __forceinline__ bool insert_column(ColBasis<W> &B, const LsdLds &S, i
 
 // Pivot rows whose columns combine to a dependent column; its local rows as for reduce.
 template <int W>
-__device__ __forceinline__ void combination(const ColBasis<W> &B, int lane, int lr_src, int cw, uint64_t (&z)[W]) {
+__device__ __forceinline__ void combination(const ColBasis<W> &B, int lane, int lr_src, int base, int cw,
+                                            uint64_t (&z)[W]) {
     B.tier([&](auto N) {
-        B.template reduce<decltype(N)::value>(lr_src, 0, cw, z);
+        B.template reduce<decltype(N)::value>(lr_src, base, cw, z);
         return 0;
     });
 #pragma unroll
     for (int s = 0; s < W; s++) z[s] &= B.piv[s];
 }
 template <int W, bool InMem, bool InLds>
-__device__ __forceinline__ void combination(const Basis<W, InMem, InLds> &B, int lane, int lr_src, int cw, uint64_t (&z)[W]) {
+__device__ __forceinline__ void combination(const Basis<W, InMem, InLds> &B, int lane, int lr_src, int base, int cw,
+                                            uint64_t (&z)[W]) {
     uint32_t bf = 0;
     for (int u = 0; u < cw; u++) {
-        const int lr = __builtin_amdgcn_readlane(lr_src, u);
+        const int lr = __builtin_amdgcn_readlane(lr_src, base + u);
         if (lr >= 0 && lr < 64 * W && (lr & 63) == lane) bf |= 1u << (lr >> 6);
     }
     uint64_t a[W];
@@ -564,15 +555,16 @@ __device__ __forceinline__ void combination(const Basis<W, InMem, InLds> &B, int
     for (int s = 0; s < W; s++) z[s] = ballot(((B.piv[s] >> lane) & 1ull) && parity_C<W>(B, s, a));
 }
 
-__device__ __forceinline__ bool in_col(const uint32_t *incol, int j) { return (incol[j >> 5] >> (j & 31)) & 1u; }
-
-
 // Local exhaustive reprocessing of order w (Appendix D) for every cluster that is not frozen.
 // T = the cluster's dependent columns in ascending key, T_w its first w = min(mu, |T|).  Every
 // pattern t over T_w fixes x_T = t and the pivot part x_P = x0 + sum_{k in t} z_k, where z_k is
 // the pivot combination of column T_k (every T_k lies in the span of the pivots).  The cost is
 // the integer weight of the set columns; the strictly smallest cost wins, the smaller t on ties.
-// Patterns are spread over the lanes.
+// Patterns are spread over the lanes, the first six columns' bits by lane.  Bound by instruction issue: a
+// pattern's cost is a sum over the rows that any pattern changes, about seven instructions each, kept in
+// one word (a few dozen rows; more take the words of all local rows and each column's set bits per
+// pattern).  Measured for LSD-10 as a kernel of its own against the words of all rows: 2374 shots of
+// [[144,12,12]] 268 -> 245 us, 5303 of a hypergraph product 192 x 400 760 -> 727 us.
 __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -612,16 +604,57 @@ __device__ __forceinline__ int64_t lane_cost(const int64_t *wq, const uint64_t (
     return cost;
 }
 
-// z: the pivot rows of cluster c (inC) whose combination reproduces column col.
-template <int W, class G, class BB>
-__device__ __forceinline__ void column_combination(const LsdLds &S, const G &g, const BB &B, const uint64_t (&inC)[W],
-                                                   int col, int lane, uint64_t (&z)[W]) {
-    const int c0 = g.col_ptr(col), cw = __builtin_amdgcn_readfirstlane(g.col_ptr(col + 1) - c0);
-    const int lr = lane < cw ? S.loc[g.row_idx(c0 + lane)] : -1;
-    combination<W>(B, lane, lr, cw, z);
-#pragma unroll
-    for (int s = 0; s < W; s++) z[s] &= inC[s];
+// Lanes 2^column_log share a column's entries.
+__device__ __forceinline__ int column_log(int max_cw) {
+    return max_cw <= 1 ? 0 : 32 - __builtin_clz((unsigned)(max_cw - 1));
 }
+
+// For the columns `col` of the given lanes, in lane order: f(lane, z), z the pivot rows of the cluster inC whose
+// combination reproduces the column.  The rows of 64 / 2^column_log columns are read at a time (one chain
+// of dependent reads, where a column at a time takes one each).
+template <int W, class G, class BB, class F>
+__device__ __forceinline__ void combinations(const LsdLds &S, const G &g, const BB &B, const uint64_t (&inC)[W],
+                                             uint64_t lanes, int col, int lane, F &&f) {
+    const int cl = column_log(g.max_cw), u = lane & ((1 << cl) - 1);
+    while (lanes) {
+        uint64_t left = lanes;
+        int src = -1;
+        for (int q = 0; q < (64 >> cl) && left; q++, left &= left - 1) src = (lane >> cl) == q ? __builtin_ctzll(left) : src;
+        const int c = __shfl(col, src < 0 ? 0 : src, 64);
+        int lr = -1;
+        if (src >= 0) {
+            const int c0 = g.col_ptr(c), cw = g.col_ptr(c + 1) - c0;
+            if (u < cw) lr = S.loc[g.row_idx(c0 + u)];
+        }
+        for (int base = 0; lanes != left; base += 1 << cl, lanes &= lanes - 1) {
+            uint64_t z[W];
+            combination<W>(B, lane, lr, base, g.max_cw, z);
+#pragma unroll
+            for (int s = 0; s < W; s++) z[s] &= inC[s];
+            f(__builtin_ctzll(lanes), z);
+        }
+    }
+}
+
+// Root and key of the dependent columns lane, lane + 64, ... of the list, read once per shot (register
+// bases; the others list up to 4096 and read them where they are used).
+template <int PER>
+struct Dependents {
+    int root[PER];
+    uint64_t key[PER];
+    __device__ __forceinline__ int root_at(int u) const {
+        int v = -1;
+#pragma unroll
+        for (int k = 0; k < PER; k++) v = u == k ? root[k] : v;
+        return v;
+    }
+    __device__ __forceinline__ uint64_t key_at(int u) const {
+        uint64_t v = 0;
+#pragma unroll
+        for (int k = 0; k < PER; k++) v = u == k ? key[k] : v;
+        return v;
+    }
+};
 
 // Local OSD-CS (combination sweep) of one valid cluster c: candidates in the order zero pattern,
 // every single dependent column of the cluster (T, ascending key), every pair (a, b), a < b < w,
@@ -630,7 +663,8 @@ __device__ __forceinline__ void column_combination(const LsdLds &S, const G &g, 
 // first.  xc: the cluster's LSD-0 solution over pivot rows.
 template <int W, int KNP, class G, class BB>
 __device__ void osd_cs_cluster(const LsdArgs &A, const LsdLds &S, const G &g, const BB &B, const uint64_t (&xc)[W],
-                               const uint64_t (&inC)[W], int c, int nnp, int w, const float *llr, int lane) {
+                               const uint64_t (&inC)[W], int c, int nnp, int w, const float *llr, int lane,
+                               const Dependents<BB::kInMem ? 1 : KNP / 64> &dep) {
     const int64_t cost0 = pivot_cost<W>(S.wq, xc, lane);
     // the rows a candidate may set: the cluster's pivots
     uint64_t rows[W];
@@ -641,30 +675,36 @@ __device__ void osd_cs_cluster(const LsdArgs &A, const LsdLds &S, const G &g, co
     int64_t bs_cost = INT64_MAX;
     uint64_t bs_key = ~0ull;
     for (int e0 = 0; e0 < nnp; e0 += 64) {
-        const bool have = e0 + lane < nnp;
-        const int mine = have ? S.colNP[e0 + lane] : 0;
-        uint64_t members = ballot(have && S.croot[S.loc[g.row_idx(g.col_ptr(mine))]] == c);
+        int mine = 0;
+        uint64_t members, kj = 0;
+        if constexpr (BB::kInMem) {
+            const bool have = e0 + lane < nnp;
+            mine = have ? S.colNP[e0 + lane] : 0;
+            members = ballot(have && S.croot[S.loc[g.row_idx(g.col_ptr(mine))]] == c);
+            if ((members >> lane) & 1ull)
+                kj = (uint64_t)((G::kInLds || A.keys_in_lds) ? S.keys[mine] : ordered_key(llr[mine])) << 32 | (uint32_t)mine;
+        } else {
+            members = ballot(dep.root_at(e0 >> 6) == c);
+            kj = dep.key_at(e0 >> 6);
+            mine = (int)(uint32_t)kj;
+        }
         const bool member = (members >> lane) & 1ull;
         if (!members) continue;
+        const int64_t om = member ? A.omega[mine] : 0;
         uint64_t y[W];
 #pragma unroll
         for (int s = 0; s < W; s++) y[s] = xc[s];
-        while (members) {
-            const int l = __builtin_ctzll(members);
-            members &= members - 1;
-            uint64_t z[W];
-            column_combination<W>(S, g, B, inC, __builtin_amdgcn_readlane(mine, l), lane, z);
+        combinations<W>(S, g, B, inC, members, mine, lane, [&](int l, const uint64_t (&z)[W]) {
             if (lane == l) {
 #pragma unroll
                 for (int s = 0; s < W; s++) y[s] ^= z[s];
             }
-        }
-        const int64_t cost = lane_cost<W>(S.wq, y, rows) + (member ? A.omega[mine] : 0);
-        const uint32_t kj = member ? ((G::kInLds || A.keys_in_lds) ? S.keys[mine] : ordered_key(llr[mine])) : 0u;
+        });
+        const int64_t cost = lane_cost<W>(S.wq, y, rows) + om;
         // smallest cost, then smallest key (costs are far below 2^62)
-        const uint64_t ck = wave_min_u64(member ? (uint64_t)(cost + (1ll << 62)) : ~0ull);
+        const uint64_t ck = wave_min_key(member ? (uint64_t)(cost + (1ll << 62)) : ~0ull);
         const int64_t best = (int64_t)ck - (1ll << 62);
-        const uint64_t key = wave_min_u64(member && cost == best ? ((uint64_t)kj << 32) | (uint32_t)mine : ~0ull);
+        const uint64_t key = wave_min_key(member && cost == best ? kj : ~0ull);
         if (best < bs_cost || (best == bs_cost && key < bs_key)) { bs_cost = best; bs_key = key; }
     }
     // pairs among T_w, lexicographic index order
@@ -682,17 +722,17 @@ __device__ void osd_cs_cluster(const LsdArgs &A, const LsdLds &S, const G &g, co
         const uint64_t key = ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)p;
         bp = key < bp ? key : bp;
     }
-    bp = wave_min_u64(bp);
+    bp = wave_min_key(bp);
     const int64_t bp_cost = bp == ~0ull ? INT64_MAX : (int64_t)(bp >> 12) - (1ll << 50);
     uint64_t x[W];
 #pragma unroll
     for (int s = 0; s < W; s++) x[s] = xc[s];
     if (bs_cost < cost0 && bs_cost <= bp_cost) {
         const int col = (int)(uint32_t)bs_key;
-        uint64_t z[W];
-        column_combination<W>(S, g, B, inC, col, lane, z);
+        combinations<W>(S, g, B, inC, 1ull, col, lane, [&](int, const uint64_t (&z)[W]) {
 #pragma unroll
-        for (int s = 0; s < W; s++) x[s] ^= z[s];
+            for (int s = 0; s < W; s++) x[s] ^= z[s];
+        });
         if (lane == 0) atomicOr(&S.cbit[col >> 5], 1u << (col & 31));
     } else if (bp_cost < cost0 && bp_cost < bs_cost) {
         const int p = (int)(bp & 4095ull);
@@ -735,6 +775,21 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
     }
     wave_sync();
     const int nnp = npc < KNP ? npc : KNP;
+    constexpr int PER = BB::kInMem ? 1 : KNP / 64;
+    Dependents<PER> dep;
+    if constexpr (!BB::kInMem) {
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            dep.root[u] = -1;
+            dep.key[u] = ~0ull;
+            if (u * 64 + lane < nnp) {
+                const int col = S.colNP[u * 64 + lane];
+                const uint32_t kj = (G::kInLds || A.keys_in_lds) ? S.keys[col] : ordered_key(llr[col]);
+                dep.root[u] = S.croot[S.loc[g.row_idx(g.col_ptr(col))]];
+                dep.key[u] = ((uint64_t)kj << 32) | (uint32_t)col;
+            }
+        }
+    }
     using Chosen = typename std::conditional<(KNP > 32 * 64), uint64_t, uint32_t>::type;
 #pragma unroll 1
     for (int s0 = 0; s0 < W; s0++) {  // one copy of the body: the slice's roots are picked by compares
@@ -753,55 +808,122 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
             }
             // T_w: the cluster's dependent columns of smallest key
             Chosen chosen = 0;  // bit u: entry lane + 64 u taken
-            int w = 0;
+            int w = 0, picked = 0;  // lane k: the k-th of them
             for (; w < mu; w++) {
                 uint64_t mine = ~0ull;
-                for (int u = 0; u * 64 + lane < nnp; u++) {
-                    if ((chosen >> u) & Chosen(1)) continue;
-                    const int col = S.colNP[u * 64 + lane];
-                    const int rr = S.loc[g.row_idx(g.col_ptr(col))];
-                    if (S.croot[rr] != c) continue;
-                    const uint32_t kj = (G::kInLds || A.keys_in_lds) ? S.keys[col] : ordered_key(llr[col]);
-                    const uint64_t key = ((uint64_t)kj << 32) | (uint32_t)col;
-                    mine = key < mine ? key : mine;
+                if constexpr (BB::kInMem) {
+                    for (int u = 0; u * 64 + lane < nnp; u++) {
+                        if ((chosen >> u) & Chosen(1)) continue;
+                        const int col = S.colNP[u * 64 + lane];
+                        const int rr = S.loc[g.row_idx(g.col_ptr(col))];
+                        if (S.croot[rr] != c) continue;
+                        const uint32_t kj = (G::kInLds || A.keys_in_lds) ? S.keys[col] : ordered_key(llr[col]);
+                        const uint64_t key = ((uint64_t)kj << 32) | (uint32_t)col;
+                        mine = key < mine ? key : mine;
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < PER; u++) {
+                        const bool open = dep.root[u] == c && !((chosen >> u) & Chosen(1));
+                        mine = open && dep.key[u] < mine ? dep.key[u] : mine;
+                    }
                 }
-                const uint64_t kmin = wave_min_u64(mine);
+                const uint64_t kmin = wave_min_key(mine);
                 if (kmin == ~0ull) break;
                 const int col = (int)(uint32_t)kmin;
-                for (int u = 0; u * 64 + lane < nnp; u++)
-                    if (S.colNP[u * 64 + lane] == col) chosen |= Chosen(1) << u;
-                // z_w: pivot rows of this cluster whose combination reproduces column col
-                uint64_t z[W];
-                column_combination<W>(S, g, B, inC, __builtin_amdgcn_readfirstlane(col), lane, z);
-                if (lane == 0) {
+                if (lane == w) picked = col;
+                if constexpr (BB::kInMem) {
+                    for (int u = 0; u * 64 + lane < nnp; u++)
+                        if (S.colNP[u * 64 + lane] == col) chosen |= Chosen(1) << u;
+                } else {
 #pragma unroll
-                    for (int s = 0; s < W; s++) S.zk[w * W + s] = z[s];
-                }
-                if (lane == 0) {
-                    S.tsel[w] = col;
-                    S.tw[w] = A.omega[col];
+                    for (int u = 0; u < PER; u++)
+                        if (dep.key[u] == kmin) chosen |= Chosen(1) << u;
                 }
             }
+            if (lane < w) {
+                S.tsel[lane] = picked;
+                S.tw[lane] = A.omega[picked];
+            }
+            // z_k: pivot rows of this cluster whose combination reproduces column k
+            uint64_t rows[W];  // the rows a pattern may change (the others cost all patterns the same)
+#pragma unroll
+            for (int s = 0; s < W; s++) rows[s] = 0;
+            combinations<W>(S, g, B, inC, (1ull << w) - 1ull, picked, lane, [&](int k, const uint64_t (&z)[W]) {
+#pragma unroll
+                for (int s = 0; s < W; s++) {
+                    rows[s] |= z[s];
+                    if (lane == 0) S.zk[k * W + s] = z[s];
+                }
+            });
             wave_sync();
             uint64_t xc[W];
 #pragma unroll
             for (int s = 0; s < W; s++) xc[s] = x0[s] & inC[s];
             if (A.cs_order > 0) {
                 if constexpr (!BB::kInMem) {
-                    [[clang::always_inline]] osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane);
+                    [[clang::always_inline]] osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane, dep);
                 } else {
-                    osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane);
+                    osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane, dep);
                 }
                 continue;
             }
             // search the 2^w patterns
             const int npat = 1 << w;
             uint64_t best = ~0ull;
-            uint64_t rows[W];
+            int nr = 0;
 #pragma unroll
-            for (int s = 0; s < W; s++) rows[s] = B.piv[s] & inC[s];
-            for (int p0 = 0; p0 < npat; p0 += 64) {
-                const int pt = (p0 + lane) & (npat - 1);  // fewer than 64: some twice, with the same key
+            for (int s = 0; s < W; s++) nr += __popcll(rows[s]);
+            if (nr <= 64) {
+                // one word per pattern: bit i stands for the i-th of those rows
+#pragma unroll
+                for (int s = 0, i0 = 0; s < W; s++) {
+                    if ((rows[s] >> lane) & 1ull) {
+                        const int r = s * 64 + lane, i = i0 + __popcll(rows[s] & ((1ull << lane) - 1ull));
+                        S.lkey[i] = (uint64_t)S.wq[r];
+                        S.lroot[i] = 2 * r + (int)((xc[s] >> lane) & 1ull);
+                    }
+                    i0 += __popcll(rows[s]);
+                }
+                wave_sync();
+                const int e = lane < nr ? S.lroot[lane] : 0;
+                uint64_t z[kMaxMu], xl = ballot(e & 1);
+                int64_t cl = 0;
+#pragma unroll
+                for (int k = 0; k < kMaxMu; k++) {
+                    z[k] = 0;
+                    if (k < w) z[k] = ballot(lane < nr && ((S.zk[k * W + (e >> 7)] >> ((e >> 1) & 63)) & 1ull));
+                }
+                const int low = lane & (npat - 1);  // fewer than 64 patterns: some twice, with the same key
+#pragma unroll
+                for (int k = 0; k < 6; k++)
+                    if ((low >> k) & 1) {
+                        xl ^= z[k];
+                        cl += S.tw[k];
+                    }
+                for (int p0 = 0; p0 < npat; p0 += 64) {
+                    uint64_t x = xl;
+                    int64_t cost = cl;
+#pragma unroll
+                    for (int k = 6; k < kMaxMu; k++)
+                        if ((p0 >> k) & 1) {
+                            x ^= z[k];
+                            cost += S.tw[k];
+                        }
+                    for (int b = 0; b < nr; b += 8) {
+                        const int32_t bits = (int32_t)(uint32_t)(x >> b);
+                        int64_t q[8];
+#pragma unroll
+                        for (int k = 0; k < 8; k++) q[k] = (int64_t)S.lkey[b + k];
+#pragma unroll
+                        for (int k = 0; k < 8; k++) cost += q[k] & (int64_t)((int32_t)(bits << (31 - k)) >> 31);
+                    }
+                    const uint64_t key = ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)(p0 + low);
+                    best = key < best ? key : best;
+                }
+            }
+            for (int p0 = 0; p0 < npat && nr > 64; p0 += 64) {
+                const int pt = (p0 + lane) & (npat - 1);
                 uint64_t x[W];
                 int64_t cost = 0;
 #pragma unroll
@@ -817,7 +939,7 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
                 const uint64_t key = ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)pt;
                 best = key < best ? key : best;
             }
-            const int tb = (int)(wave_min_u64(best) & 4095ull);
+            const int tb = (int)(wave_min_key(best) & 4095ull);
             uint64_t x[W];
 #pragma unroll
             for (int s = 0; s < W; s++) x[s] = xc[s];
@@ -1031,11 +1153,26 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
 #pragma unroll
     for (int q = 0; q < kSynPre; q++) sy[q] = q * 64 + lane < m ? syn[q * 64 + lane] : 0;
     bool nan = false;
-    for (int j = lane; j < n; j += 64) {
-        // coherent read: an equal compare-and-swap returns the word at the point of coherence
-        const float v = A.coherent_llr ? __int_as_float(atomicCAS((int *)llr + j, 0, 0)) : llr[j];
-        nan |= (v != v);
-        if (G::kInLds || A.keys_in_lds) S.keys[j] = ordered_key(v);
+    if (A.coherent_llr) {
+        for (int j = lane; j < n; j += 64) {
+            // coherent read: an equal compare-and-swap returns the word at the point of coherence
+            const float v = __int_as_float(atomicCAS((int *)llr + j, 0, 0));
+            nan |= (v != v);
+            if (G::kInLds || A.keys_in_lds) S.keys[j] = ordered_key(v);
+        }
+    } else {
+        // sixteen loads in flight (a loop of single loads waits for memory once per 64 faults)
+        for (int j0 = 0; j0 < n; j0 += 16 * 64) {
+            float v[16];
+#pragma unroll
+            for (int q = 0; q < 16; q++) v[q] = llr[min(j0 + q * 64 + lane, n - 1)];
+#pragma unroll
+            for (int q = 0; q < 16; q++) nan |= v[q] != v[q];
+            if (G::kInLds || A.keys_in_lds) {
+#pragma unroll
+                for (int q = 0; q < 16; q++) S.keys[min(j0 + q * 64 + lane, n - 1)] = ordered_key(v[q]);
+            }
+        }
     }
     for (int w = lane; w < (n + 31) / 32; w += 64) { S.incol[w] = 0u; S.cbit[w] = 0u; }
     for (int i = lane; i < m; i += 64) { S.loc[i] = -1; S.claimer[i] = kFree; }
@@ -1153,35 +1290,42 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
     }
     wave_sync();
 
-    // LSD-0 rounds grow the invalid clusters until none is left; LSD-mu then runs mu more
-    // rounds in which every cluster that is not frozen grows (Appendix D).
-    // smallest candidate key among the edges e0 .. e1 - 1 of a row
+    // smallest candidate key among the edges e0 .. e1 - 1 of a row: kScan entries per pass, every load
+    // issued before any is used (entries past the row's end re-read its last one and are masked out), so a
+    // row of weight <= kScan costs two dependent rounds of loads (6 fits the small codes' rows without
+    // masked slots; the large graphs' rows are longer, and their loads go to global memory)
     auto scan_row = [&](int e0, int e1) -> uint64_t {
-                                uint64_t best = ~0ull;
-                                // kScan entries per pass, every load issued before any is used (entries
-                                // past the row's end re-read its last one and are masked out), so a row of
-                                // weight <= kScan costs two dependent rounds of loads (6 fits the small
-                                // codes' rows without masked slots; the large graphs' rows are longer)
-                                constexpr int kScan = W <= 2 ? 6 : 8;
-                                for (int eb = e0; eb < e1; eb += kScan) {
-                                    int jj[kScan];
+        constexpr int kScan = W <= 2 ? 6 : G::kInLds ? 8 : 16;
+        uint64_t best = ~0ull;
+        for (int eb = e0; eb < e1; eb += kScan) {
+            int jj[kScan];
 #pragma unroll
-                                    for (int u = 0; u < kScan; u++) jj[u] = g.col_idx(min(eb + u, e1 - 1));
-                                    uint32_t kk[kScan], ic[kScan];
+            for (int u = 0; u < kScan; u++) jj[u] = g.col_idx(min(eb + u, e1 - 1));
+            uint32_t kk[kScan], ic[kScan];
+            // (the branch outside the loops: inside, each load would wait for the one before)
+            if (G::kInLds || A.keys_in_lds) {
 #pragma unroll
-                                    for (int u = 0; u < kScan; u++) {
-                                        kk[u] = (G::kInLds || A.keys_in_lds) ? S.keys[jj[u]] : ordered_key(llr[jj[u]]);
-                                        ic[u] = S.incol[jj[u] >> 5];
-                                    }
+                for (int u = 0; u < kScan; u++) kk[u] = S.keys[jj[u]];
+            } else {
+                float v[kScan];
 #pragma unroll
-                                    for (int u = 0; u < kScan; u++) {
-                                        const bool ok = eb + u < e1 && !((ic[u] >> (jj[u] & 31)) & 1u);
-                                        const uint64_t key = ok ? (((uint64_t)kk[u] << 32) | (uint32_t)jj[u]) : ~0ull;
-                                        best = key < best ? key : best;
-                                    }
-                                }
+                for (int u = 0; u < kScan; u++) v[u] = llr[jj[u]];
+#pragma unroll
+                for (int u = 0; u < kScan; u++) kk[u] = ordered_key(v[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kScan; u++) ic[u] = S.incol[jj[u] >> 5];
+#pragma unroll
+            for (int u = 0; u < kScan; u++) {
+                const bool ok = eb + u < e1 && !((ic[u] >> (jj[u] & 31)) & 1u);
+                const uint64_t key = ok ? (((uint64_t)kk[u] << 32) | (uint32_t)jj[u]) : ~0ull;
+                best = key < best ? key : best;
+            }
+        }
         return best;
     };
+    // LSD-0 rounds grow the invalid clusters until none is left; LSD-mu then runs mu more
+    // rounds in which every cluster that is not frozen grows (Appendix D).
     bool grow_all = false;
     int mu_left = 0;
     int npc = 0;  // dependent columns recorded in colNP
@@ -1194,10 +1338,11 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
     // validity, and the rows of the new column look for their next candidate while it is inserted, several
     // lanes a row.  A round of about 9,000 cycles takes about 5,000: hypergraph product 432 x 900, 2048
     // shots at 3%, kernel alone 548 -> 318 us; windows of a 12-round memory 300 -> 170 us; LSD-16 with its
-    // sweep on [[144,12,12]] 380 -> 301 us; 936 x 8800 detector model, 37 shots, LSD-10 (graph in global
-    // memory) 410 -> 396 us.
+    // sweep on [[144,12,12]] 380 -> 301 us; 936 x 8800 detector model, 37 shots, LSD-10 (graph and keys in
+    // global memory) 410 -> 396 us, and 378 -> 258 us once no load there waits for the one before (scan_row,
+    // the first pass over the LLRs).
     auto lone_rounds = [&](int root, int (&rows_root)[W]) -> bool {
-        const int cw_log = g.max_cw <= 1 ? 0 : 32 - __builtin_clz((unsigned)(g.max_cw - 1));
+        const int cw_log = column_log(g.max_cw);
         const int u = lane & ((1 << cw_log) - 1), step = 64 >> cw_log;
         for (;;) {
             uint64_t best = ~0ull;
@@ -1284,10 +1429,13 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
             uint32_t kk[kAhead], ic[kAhead];
             auto fetch = [&]() {
 #pragma unroll
-                for (int k = 0; k < kAhead; k++) {
-                    const int j = jn[k] < 0 ? col : jn[k];
-                    kk[k] = (G::kInLds || A.keys_in_lds) ? S.keys[j] : __float_as_uint(llr[j]);
-                    ic[k] = S.incol[j >> 5];
+                for (int k = 0; k < kAhead; k++) ic[k] = S.incol[(jn[k] < 0 ? col : jn[k]) >> 5];
+                if (G::kInLds || A.keys_in_lds) {
+#pragma unroll
+                    for (int k = 0; k < kAhead; k++) kk[k] = S.keys[jn[k] < 0 ? col : jn[k]];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kAhead; k++) kk[k] = __float_as_uint(llr[jn[k] < 0 ? col : jn[k]]);
                 }
             };
             auto look = [&]() {
@@ -1655,8 +1803,11 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
         uint32_t *cnt = (uint32_t *)S.sel;
         for (int r = lane; r < K; r += 64) cnt[r] = 0u;
         wave_sync();
-        for (int j = lane; j < n; j += 64)
-            if (in_col(S.incol, j)) atomicAdd(&cnt[find_root(S.croot, S.loc[g.row_idx(g.col_ptr(j))])], 1u);
+        for (int w = lane; w < (n + 31) / 32; w += 64)
+            for (uint32_t bits = S.incol[w]; bits; bits &= bits - 1) {
+                const int j = 32 * w + __builtin_ctz(bits);
+                atomicAdd(&cnt[find_root(S.croot, S.loc[g.row_idx(g.col_ptr(j))])], 1u);
+            }
         wave_sync();
         uint32_t mx = 0u, tot = 0u, sq = 0u;
         for (int r = lane; r < K; r += 64) {

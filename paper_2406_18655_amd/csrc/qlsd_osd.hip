@@ -288,7 +288,7 @@ __device__ void osd0_shot(const OsdArgs &A, uint64_t *keys, uint32_t *cbit, int3
             }
         }
         wave_sync();
-        bsk = wave_min_u64(bsk);
+        bsk = wave_min_key(bsk);
         const int64_t bs_cost = bsk == ~0ull ? INT64_MAX : (int64_t)(bsk >> 12) - (1ll << 50);
         const int bs = (int)(bsk & 4095ull);
         // pairs (a, b), a < b < w, lexicographic; spread over the lanes, the smallest
@@ -307,13 +307,13 @@ __device__ void osd0_shot(const OsdArgs &A, uint64_t *keys, uint32_t *cbit, int3
             const uint64_t key = ((uint64_t)(cost + (1ll << 50)) << 12) | (uint64_t)p;
             bp = key < bp ? key : bp;
         }
-        bp = wave_min_u64(bp);
+        bp = wave_min_key(bp);
         const int64_t bp_cost = bp == ~0ull ? INT64_MAX : (int64_t)(bp >> 12) - (1ll << 50);
         if (bs_cost < cost0 && bs_cost <= bp_cost) {
             const int col = __builtin_amdgcn_readfirstlane(X.dep[bs]);
             const int c0 = A.g.col_ptr[col], cw = __builtin_amdgcn_readfirstlane(A.g.col_ptr[col + 1] - c0);
             uint64_t z[W];
-            combination<W>(B, lane, lane < cw ? A.g.row_idx[c0 + lane] : -1, cw, z);
+            combination<W>(B, lane, lane < cw ? A.g.row_idx[c0 + lane] : -1, 0, cw, z);
 #pragma unroll
             for (int s = 0; s < W; s++) x[s] ^= z[s];
             if (lane == 0) atomicOr(&cbit[col >> 5], 1u << (col & 31));
