@@ -16,6 +16,7 @@
 // number of work items shrinks only once the queue is empty.  HBM traffic is only the syndrome
 // in, the correction out, and the posterior LLRs of shots that go on to LSD.
 #include <algorithm>
+#include <climits>
 #include <functional>
 #include <cstring>
 #include <type_traits>
@@ -894,14 +895,16 @@ int bp_min_stride(const DevGraph &g) { return odd_stride(g.nnz); }
 // lanes: a message access costs, per half, the largest number of its lanes whose words fall in one
 // bank.  Lane t of a phase serves slot t mod S of check (or fault) t div S, so the lanes of a
 // wavefront read edge u of a few consecutive checks (faults) in every slot, at slot * SE + edge.
+// A count that reaches `limit` stops there (a stride that is no better need not be counted to the end:
+// decoder creation on the 432 x 900 graph 8.7 -> 6.2 ms).
 static long long bp_bank_cycles(const int32_t *row_ptr, const int32_t *col_ptr, const int32_t *col_edge, int m,
-                                int n, int max_rw, int max_cw, int S, int SE, int threads) {
+                                int n, int max_rw, int max_cw, int S, int SE, int threads, long long limit) {
     long long cyc = 0;
     int bank[32];
     auto pass = [&](int items, int first_thread, int max_w, auto addr) {
         const int NT = threads - first_thread;     // threads of the phase
         const int R = NT / S;                      // items per step
-        for (int it = 0; it < items; it += R)
+        for (int it = 0; it < items && cyc < limit; it += R)
             for (int w0 = 0; w0 < NT; w0 += 64)
                 for (int u = 0; u < max_w; u++)
                     for (int h = 0; h < 64; h += 32) {
@@ -940,7 +943,8 @@ int bp_msg_stride(const DevGraph &g, const int32_t *row_ptr, const int32_t *col_
     long long best_cyc = -1;
     for (int SE = g.nnz; SE < g.nnz + 64; SE++) {
         if (bp_lds_bytes(g, S, SE) > budget) break;
-        const long long c = bp_bank_cycles(row_ptr, col_ptr, col_edge, g.m, g.n, g.max_rw, g.max_cw, S, SE, threads);
+        const long long c = bp_bank_cycles(row_ptr, col_ptr, col_edge, g.m, g.n, g.max_rw, g.max_cw, S, SE, threads,
+                                           best_cyc < 0 ? LLONG_MAX : best_cyc);
         if (best_cyc < 0 || c < best_cyc) { best_cyc = c; best = SE; }
     }
     return best;
