@@ -220,7 +220,7 @@ def main():
         if tj.get("kernel_source_hash") == _kernel_hash():
             traffic = tj.get("bytes_per_launch")
     roofline = {"bound": "hbm",
-                "kernel": "bp_graph2_kernel" if dem else "bp_lds_kernel (BP + LSD-0 in one kernel)",
+                "kernel": "bp_graph3_kernel" if dem else "bp_lds_kernel (BP + LSD-0 in one kernel)",
                 "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "avg_launch_ms": round(bp_avg_ms, 4),
@@ -451,13 +451,13 @@ def record_counters(pass1, pass2, path):
         rows = list(csv.DictReader(open(fn)))
         by = {}
         for r in rows:
-            if "bp_lds_kernel<6, 3, true, 2, false>" not in r.get("Kernel_Name", ""):
+            if "bp_lds_kernel<6, 3, true, 2, false, 256>" not in r.get("Kernel_Name", ""):
                 continue
             by.setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
         for k, v in by.items():
             vals[k] = float(np.median(v))
     vals["kernel_source_hash"] = _kernel_hash()
-    vals["kernel"] = "bp_lds_kernel<6, 3, true, 2, false> (BP 50 + LSD-0 in one kernel)"
+    vals["kernel"] = "bp_lds_kernel<6, 3, true, 2, false, 256> (BP 50 + LSD-0 in one kernel)"
     with open(path, "w") as f:
         json.dump(vals, f, indent=1)
     print(json.dumps(vals))
@@ -518,15 +518,15 @@ def record_traffic(fetch, write, cfetch, cwrite, path):
         v = [float(r["Counter_Value"]) for r in csv.DictReader(open(fn)) if needle in r.get("Kernel_Name", "")]
         return v
 
-    f_k = float(np.median(per_dispatch(fetch, "bp_lds_kernel<6, 3, true, 2, false>")))
-    w_k = float(np.median(per_dispatch(write, "bp_lds_kernel<6, 3, true, 2, false>")))
+    f_k = float(np.median(per_dispatch(fetch, "bp_lds_kernel<6, 3, true, 2, false, 256>")))
+    w_k = float(np.median(per_dispatch(write, "bp_lds_kernel<6, 3, true, 2, false, 256>")))
     # the 1 GiB copies (the calibration run's last, tiny copy returns a flag to the host)
     cf = [v for v in per_dispatch(cfetch, "copyBuffer") if v > 1024.0]
     cw = [v for v in per_dispatch(cwrite, "copyBuffer") if v > 1024.0]
     nbytes = 1 << 30
     f_fac = nbytes / 1024.0 / float(np.mean(cf))
     w_fac = nbytes / 1024.0 / float(np.mean(cw))
-    rec = {"kernel": "bp_lds_kernel<6,3,true,2,false> (BP + LSD-0 in one kernel)",
+    rec = {"kernel": "bp_lds_kernel<6,3,true,2,false,256> (BP + LSD-0 in one kernel)",
            "workload": "bb144_codecap_p0.05_bp50_lsd0, 65536 shots per launch",
            "kernel_source_hash": _kernel_hash(),
            "bytes_per_launch": round(1024.0 * (f_k * f_fac + w_k * w_fac)),
@@ -658,7 +658,7 @@ def _kernel_hash(root=None):
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in ("qlsd_bp.hip", "qlsd_internal.h", "qlsd_lsd_dev.h"):
+    for f in ("qlsd_bp.hip", "qlsd_internal.h", "qlsd_lsd_dev.h", "qlsd_lsd_small.h"):
         with open(os.path.join(root or HERE, "paper_2406_18655_amd", "csrc", f), encoding="utf-8") as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)

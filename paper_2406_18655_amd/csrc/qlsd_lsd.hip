@@ -16,12 +16,13 @@
 // cluster, and all reductions happen in a single Gauss-Jordan basis over those rows.  Columns of
 // different clusters never share a row, so this is exactly the block-diagonal form that the
 // paper's merge step (Sec. 4.2, block swap of zero rows) produces -- a merge costs nothing.
-// The basis is bit-sliced across the wavefront: lane l holds local rows l, l+64, ... and, for
-// each, the row's bits over the pivot rows (Mrow) and, for the column that created each pivot,
-// the pivots whose combination contains it (CT).  Reducing a new column, adding a pivot and
-// solving are then per-lane AND/XOR/popcount plus a few ballots -- no cross-lane reductions.
+// The basis is bit-sliced across the wavefront: lane l holds local rows l, l+64, ... and, for each,
+// the image of the row's unit vector under all eliminations so far (ColBasis): a column is reduced by
+// the exclusive or of its rows' images, a pivot updates every image that has its bit.  The overflow
+// kernels and the cluster-batched schedule keep the transform by rows instead (Basis).
 // Union-find over local rows lives in LDS (lock-free CAS hooking of the larger root under the
-// smaller one); candidate selection is a per-row scan plus an LDS 64-bit atomic min per root.
+// smaller one); candidate selection is a per-row scan plus an LDS 64-bit atomic min per root.  Small codes
+// take decode_small, and rounds with one growing cluster a loop of their own in decode_shot.
 #include <algorithm>
 
 #include "qlsd_lsd_small.h"
