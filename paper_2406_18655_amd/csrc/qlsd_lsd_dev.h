@@ -1362,7 +1362,8 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
             }
             const uint64_t pick = wave_min_key(best);
             if (pick == ~0ull) {
-                if (lane == 0) S.state[root] = kFrozen;
+                // (the count too: the rounds of LSD-mu number their new rows from it)
+                if (lane == 0) { S.state[root] = kFrozen; S.ctl[0] = nrows; }
                 status |= QLSD_ST_UNSAT;
                 wave_sync();
                 return true;

@@ -158,3 +158,53 @@ def test_lsd_of_lone_clusters(oracle_mod, m, n, heavy, mu):
             assert inf["rounds"][b] == stats[2], b
         most = max(most, int(inf["rounds"][b]))
     print(f"  rounds up to {most}")
+
+
+def _blocks(chain, copies, weight):
+    """A chain of `chain` checks, two faults between neighbours (a syndrome of odd weight is outside its
+    image), beside `copies` blocks of `weight` checks with one fault on each check and one on all."""
+    m, n = chain + copies * weight, 2 * (chain - 1) + copies * (weight + 1)
+    H = np.zeros((m, n), dtype=np.uint8)
+    for i in range(chain - 1):
+        H[i:i + 2, 2 * i:2 * i + 2] = 1
+    for k in range(copies):
+        r, c = chain + k * weight, 2 * (chain - 1) + k * (weight + 1)
+        H[r + np.arange(weight), c + np.arange(weight)] = 1
+        H[r:r + weight, c + weight] = 1
+    return H
+
+
+# LSD-mu after a cluster that grew alone has found no fault left: its rounds of all other clusters take more
+# (cluster, check) pairs than a wavefront has lanes (22 clusters of column weight 3, 5 of weight 16), or fewer
+@pytest.mark.parametrize("chain,copies,weight,mu", [(3, 30, 3, 1), (40, 30, 3, 3), (70, 60, 3, 2), (40, 6, 16, 2),
+                                                    (9, 12, 16, 5), (40, 4, 3, 2)])
+def test_lsd_mu_after_a_frozen_cluster(oracle_mod, chain, copies, weight, mu):
+    print(f"case lsd_shapes frozen chain {chain} copies {copies} weight {weight} mu {mu}", flush=True)
+    H = _blocks(chain, copies, weight)
+    m, n = H.shape
+    rng = np.random.default_rng(m + n)
+    B, first = 24, 2 * (chain - 1)
+    S = np.zeros((B, m), dtype=np.uint8)
+    L = rng.normal(3.0, 0.5, size=(B, n)).astype(np.float32)
+    starts = chain + weight * np.arange(copies)
+    for b in range(B):
+        S[b, rng.choice(chain, size=1 + 2 * (b % 2), replace=False)] = 1
+        # every block, or all but a few: a check of it, whose own fault is the likeliest of the block
+        some = starts[rng.permutation(copies)[b % 3:]]
+        S[b, some] = 1
+        L[b, first + (some - chain) // weight * (weight + 1)] = 1.0
+    L[1::4, first:] = np.rint(L[1::4, first:])
+    bc = binding.Code.from_dense(H)
+    priors = np.random.default_rng(7).uniform(0.01, 0.2, size=n)
+    dec = binding.Decoder(bc, priors, B, max_iter=5, lsd_order=mu)
+    corr, info, st = dec.lsd_stats(torch.from_numpy(S).cuda(), torch.from_numpy(L).cuda())
+    torch.cuda.synchronize()
+    c, st, inf = corr.cpu().numpy(), st.cpu().numpy(), binding.parse_info(info)
+    oc = oracle_mod.Code.from_dense(H)
+    om = oracle_mod.omega_from_llr(oracle_mod.llr_from_priors(priors))
+    for b in range(B):
+        want, ost, stats = oracle_mod.lsd(oc, S[b], L[b].astype(np.float64), mu=mu, omega=om)
+        assert ost & oracle_mod.ST_UNSAT and inf["status"][b] & binding.ST_UNSAT, b
+        assert not inf["status"][b] & (binding.ST_OVERFLOW | binding.ST_BAD_LLR), b
+        assert (c[b] == want).all(), b
+        assert tuple(st[b]) == (stats[0], stats[1], stats[3], stats[6]), b
