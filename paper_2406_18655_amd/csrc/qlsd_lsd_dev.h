@@ -660,11 +660,14 @@ struct Dependents {
 // every single dependent column of the cluster (T, ascending key), every pair (a, b), a < b < w,
 // of its first w dependent columns (T_w, already selected into tsel/zk/tw); each scored by the
 // integer weight of its solution; the strictly smallest cost wins, ties to the candidate met
-// first.  xc: the cluster's LSD-0 solution over pivot rows.
+// first.  xc: the cluster's LSD-0 solution over pivot rows.  Inlined everywhere: as a call inside the call of
+// osd_e_clusters its registers cost the wide kernel's growth rounds theirs (1138 spilled; LSD-1 of 16 shots
+// of the 936 x 8800 detector error model 130 ms, inlined 86).
 template <int W, int KNP, class G, class BB>
-__device__ void osd_cs_cluster(const LsdArgs &A, const LsdLds &S, const G &g, const BB &B, const uint64_t (&xc)[W],
-                               const uint64_t (&inC)[W], int c, int nnp, int w, const float *llr, int lane,
-                               const Dependents<BB::kInMem ? 1 : KNP / 64> &dep) {
+__device__ __forceinline__ void osd_cs_cluster(const LsdArgs &A, const LsdLds &S, const G &g, const BB &B,
+                                               const uint64_t (&xc)[W], const uint64_t (&inC)[W], int c, int nnp,
+                                               int w, const float *llr, int lane,
+                                               const Dependents<BB::kInMem ? 1 : KNP / 64> &dep) {
     const int64_t cost0 = pivot_cost<W>(S.wq, xc, lane);
     // the rows a candidate may set: the cluster's pivots
     uint64_t rows[W];
@@ -861,11 +864,7 @@ __device__ void osd_e_clusters(const LsdArgs &A, const LsdLds &S, const G &g, co
 #pragma unroll
             for (int s = 0; s < W; s++) xc[s] = x0[s] & inC[s];
             if (A.cs_order > 0) {
-                if constexpr (!BB::kInMem) {
-                    [[clang::always_inline]] osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane, dep);
-                } else {
-                    osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane, dep);
-                }
+                osd_cs_cluster<W, KNP>(A, S, g, B, xc, inC, c, nnp, w, llr, lane, dep);
                 continue;
             }
             // search the 2^w patterns

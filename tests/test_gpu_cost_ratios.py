@@ -1,0 +1,48 @@
+"""Ratios of two timings on one device, for calls whose cost has to follow another's: a kernel that falls
+off its path (registers in memory, one thread where a wavefront belongs) shows here and in no result."""
+import numpy as np
+import pytest
+
+from paper_2406_18655_amd import binding
+from paper_2406_18655_amd.workloads import synthetic_dem
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.lib()
+
+
+def _ms(call, passes=1):
+    """Shortest of five measurements of `passes` calls, in ms a call."""
+    call()
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(passes):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / passes)
+    return best
+
+
+def test_lsd_mu_rounds_of_wide_shots():
+    """Shots of the detector error model whose clusters outgrow 512 rows: the rounds are nearly all of
+    LSD-1's time, so it stays close to LSD-0's (0.9 of it; 1.3 where the sweep's calls cost the rounds
+    their registers)."""
+    print("case cost wide lsd-mu", flush=True)
+    code = synthetic_dem()
+    rng = np.random.default_rng(7)
+    E = (rng.random((8, code.n)) < 0.003).astype(np.int32)
+    s = torch.from_numpy((E @ code.H.T.astype(np.int32) % 2).astype(np.uint8)).cuda()
+    llr = torch.from_numpy((rng.normal(3, 2, E.shape) - 3 * E).astype(np.float32)).cuda()
+    bc = binding.Code.from_dense(code.H)
+    t = [_ms(lambda d=binding.Decoder(bc, code.priors, 8, max_iter=10, lsd_order=mu): d.lsd(s, llr)) for mu in (0, 1)]
+    print(f"  LSD-0 {t[0]:.1f} ms, LSD-1 {t[1]:.1f} ms")
+    assert t[1] <= 1.15 * t[0]
