@@ -1292,9 +1292,10 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
     // smallest candidate key among the edges e0 .. e1 - 1 of a row: kScan entries per pass, every load
     // issued before any is used (entries past the row's end re-read its last one and are masked out), so a
     // row of weight <= kScan costs two dependent rounds of loads (6 fits the small codes' rows without
-    // masked slots; the large graphs' rows are longer, and their loads go to global memory)
+    // masked slots; the large graphs' rows are longer, and their loads go to global memory: 16 make 37
+    // shots of the 936 x 8800 detector error model 2% faster, but cost the wide kernel 30 registers)
     auto scan_row = [&](int e0, int e1) -> uint64_t {
-        constexpr int kScan = W <= 2 ? 6 : G::kInLds ? 8 : 16;
+        constexpr int kScan = W <= 2 ? 6 : G::kInLds || WIDE ? 8 : 16;
         uint64_t best = ~0ull;
         for (int eb = e0; eb < e1; eb += kScan) {
             int jj[kScan];
@@ -1761,6 +1762,7 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
         wave_sync();
         uint64_t any_inv = 0;
         int ninv = 0, inv_root = 0;
+        bool inv_mine = false;
 #pragma unroll
         for (int s = 0; s < W; s++) {
             const int r = s * 64 + lane;
@@ -1769,11 +1771,16 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
                 inv = vmark[r] == stamp;
                 S.state[r] = inv ? kInvalid : kValid;
             }
-            const uint64_t bal = ballot(inv);
-            any_inv |= bal;
-            ninv += __popcll(bal);
-            if (bal) inv_root = s * 64 + __builtin_ctzll(bal);
+            if constexpr (LONE) {  // how many and which, for the rounds of one alone
+                const uint64_t bal = ballot(inv);
+                any_inv |= bal;
+                ninv += __popcll(bal);
+                if (bal) inv_root = s * 64 + __builtin_ctzll(bal);
+            } else {
+                inv_mine |= inv;
+            }
         }
+        if constexpr (!LONE) any_inv = ballot(inv_mine);
         wave_sync();
         rounds++;
         if (MU && grow_all) {
@@ -1859,8 +1866,10 @@ __device__ __forceinline__ void decode_shot(const LsdArgs &A, const LsdLds &S, c
         finish(status, ncl, max_cluster_cols(ncl));
         return;
     }
-    // (a call would pass the register basis through memory)
-    if constexpr (MU && !BB::kInMem) {
+    // (a call would pass the column basis through memory; inlined into the cluster-batched kernels, whose
+    // registers the row basis fills, it makes their rounds spill: LSD-3 of 3000 shots of a hypergraph product
+    // 192 x 400 with that schedule 2.24 ms, as a call 2.17)
+    if constexpr (MU && COLS) {
         [[clang::always_inline]] osd_e_clusters<W, KNP>(A, S, g, B, x0, nrows, npc, llr, lane);
     } else if constexpr (MU) {
         osd_e_clusters<W, KNP>(A, S, g, B, x0, nrows, npc, llr, lane);
