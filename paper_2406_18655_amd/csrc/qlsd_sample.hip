@@ -21,6 +21,8 @@ struct qlsd_sampler_s {
     DevGraph g;
     uint64_t *d_thr;   // n: a fault flips iff its 64-bit output is below this
     int k;             // logical rows (0: word error)
+    int parts;         // threads that share a logical row (failure_kernel)
+    int64_t ones, steps;  // entries of the logical rows; 64-entry steps of failure_wide_kernel over a shot
     int *d_lrp, *d_lci;
 };
 
@@ -172,13 +174,19 @@ __global__ void syndrome_kernel(const int32_t *row_ptr, const int32_t *col_idx, 
     }
 }
 
-// Residual parity against each logical row (k = 0: any nonzero fault), 32 shots a word.
+// Residual parity against each logical row (k = 0: any nonzero fault), 32 shots a word.  `parts` threads
+// share a row of one group (1: rows of at most kPart entries): one thread per row takes 380 us for a single
+// row of 4,400 entries, where the rest takes 12.
+constexpr int kPart = 16;
 __global__ void failure_kernel(const uint8_t *e, const uint8_t *c, int n, int B, int k, const int *lrp, const int *lci,
-                               int words, uint8_t *fail) {
+                               int parts, int words, uint8_t *fail) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *bits = (uint32_t *)smem, *fw = bits + (size_t)n * words;
+    uint32_t *par = fw + words;  // parts > 1: each row's parity, k per group
     const int64_t shot0 = (int64_t)blockIdx.x * 32 * words;
     if (threadIdx.x < words) fw[threadIdx.x] = 0u;
+    if (parts > 1)
+        for (int it = threadIdx.x; it < k * words; it += blockDim.x) par[it] = 0u;
     slice_rows<true>(e, c, n, B, shot0, words, bits);
     __syncthreads();
     if (k == 0) {
@@ -188,11 +196,17 @@ __global__ void failure_kernel(const uint8_t *e, const uint8_t *c, int n, int B,
             if (any) atomicOr(&fw[g], any);
         }
     } else {
-        for (int it = threadIdx.x; it < k * words; it += blockDim.x) {
-            const int q = it / words, g = it - q * words;
+        for (int64_t it = threadIdx.x; it < (int64_t)k * words * parts; it += blockDim.x) {
+            const int row = (int)(it / parts), q = row / words, g = row - q * words;
             uint32_t acc = 0u;
-            for (int x = lrp[q]; x < lrp[q + 1]; x++) acc ^= bits[lci[x] * words + g];
-            if (acc) atomicOr(&fw[g], acc);
+            for (int x = lrp[q] + (int)(it - (int64_t)row * parts); x < lrp[q + 1]; x += parts) acc ^= bits[lci[x] * words + g];
+            if (acc && parts == 1) atomicOr(&fw[g], acc);
+            if (acc && parts > 1) atomicXor(&par[row], acc);
+        }
+        if (parts > 1) {
+            __syncthreads();
+            for (int it = threadIdx.x; it < k * words; it += blockDim.x)
+                if (par[it]) atomicOr(&fw[it % words], par[it]);
         }
     }
     __syncthreads();
@@ -200,8 +214,8 @@ __global__ void failure_kernel(const uint8_t *e, const uint8_t *c, int n, int B,
     for (int b = threadIdx.x; b < shots; b += blockDim.x) fail[shot0 + b] = (uint8_t)((fw[b >> 5] >> (b & 31)) & 1u);
 }
 
-// For matrices whose bit-sliced shots do not fit in LDS (more than about 35,000 faults): a thread per
-// (shot, detector), and a wavefront per shot.
+// For matrices whose bit-sliced shots do not fit in LDS (more than about 35,000 faults), and where they
+// are faster (failures_by_shot): a thread per (shot, detector), and a wavefront per shot.
 __global__ void syndrome_wide_kernel(const int32_t *row_ptr, const int32_t *col_idx, int m, int n, int B,
                                      const uint8_t *x, uint8_t *s) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -250,6 +264,23 @@ Slices slices_for(int n, int extra, int B) {
     return s;
 }
 
+// Whether failure_wide_kernel is the faster one: it reads only the entries of the logical rows, the
+// bit-sliced kernel every fault, 32 shots to a workgroup at least.  Its time follows the 64-entry steps of
+// a shot, one after the other (every row waits for the one before), the steps of all shots and the cache
+// lines they touch; the sliced kernel's the whole rows.  In us beyond a launch, fitted to both kernels over
+// 41 to 8,800 faults, no, 1 to 64 logical rows of 5 to 4,400 entries and 8 to 65,536 shots (the slower one
+// costs up to 5x: 65,536 shots of 2,000 faults with one row of 5, 14 us against 60; 20,000 shots of 2,000
+// faults with 64 rows of 40, 308 against 24; 200 shots of 8,800 with 8 rows of 1,100, 33 against 15).  Over
+// that grid the choice is within 14% of the faster one but for a single row of thousands (up to 1.9x).
+bool failures_by_shot(int n, int k, int64_t ones, int64_t steps, int B) {
+    const double rows = k > 0 ? k : 1, lines = std::min(2.0 * (k > 0 ? (double)ones : (double)n), n / 64.0 + 2.0);
+    const double chain = rows + 0.35 * ((double)steps - rows);
+    const double shot = 0.3 * std::max(chain - 8.0, 0.0) + (2.5e-5 * (double)steps + 2e-5 * lines) * B;
+    const double wide = (n > 1024 ? 2.0 : 0.0) + (n > 4096 ? 3.0 : 0.0);
+    const double sliced = 4.0 + wide * std::min(B, 32) / 32.0 + (double)B * n / 2.8e6;
+    return shot <= sliced;
+}
+
 qlsd_status sfail(qlsd_status st, const char *fmt, ...) {
     va_list ap;
     va_start(ap, fmt);
@@ -282,6 +313,15 @@ qlsd_status qlsd_sampler_create(qlsd_code code, const double *priors, int32_t k,
     s->code = code;
     s->g = g;
     s->k = k;
+    int heaviest = 0;
+    s->ones = nl;
+    s->steps = k > 0 ? 0 : (g.n + 63) / 64;
+    for (int q = 0; q < k; q++) {
+        const int w = l_row_ptr[q + 1] - l_row_ptr[q];
+        heaviest = std::max(heaviest, w);
+        s->steps += (w + 63) / 64;
+    }
+    s->parts = std::max(1, (heaviest + kPart - 1) / kPart);
     // (x >> 11) 2^-53 < p  <=>  x >> 11 < ceil(2^53 p)  <=>  x < ceil(2^53 p) << 11; p < 1, so 2^53 p, which
     // is exact, is below 2^53
     uint64_t *thr = new (std::nothrow) uint64_t[g.n];
@@ -354,14 +394,14 @@ qlsd_status qlsd_failures(qlsd_sampler s, const uint8_t *errors, const uint8_t *
     set_last_error("");
     if (!s || B < 0 || (B > 0 && (!errors || !corrections || !fail))) return sfail(QLSD_E_INVALID, "bad failure call");
     if (B == 0) return QLSD_OK;
-    const Slices k = slices_for(s->g.n, 1, B);
+    const Slices k = slices_for(s->g.n, s->parts > 1 ? 1 + s->k : 1, B);
     hipError_t e = hipSuccess;
-    if (k.words > 0) {
+    if (k.words > 0 && !failures_by_shot(s->g.n, s->k, s->ones, s->steps, B)) {
         e = hipFuncSetAttribute((const void *)failure_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
         if (e != hipSuccess) return sfail(QLSD_E_DEVICE, "failure launch: %s", hipGetErrorString(e));
         const int64_t shots = 32ll * k.words;
         hipLaunchKernelGGL(failure_kernel, dim3((unsigned)((B + shots - 1) / shots)), dim3(k.threads), k.lds,
-                           (hipStream_t)stream, errors, corrections, s->g.n, B, s->k, s->d_lrp, s->d_lci, k.words, fail);
+                           (hipStream_t)stream, errors, corrections, s->g.n, B, s->k, s->d_lrp, s->d_lci, s->parts, k.words, fail);
     } else {
         hipLaunchKernelGGL(failure_wide_kernel, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, (hipStream_t)stream, errors,
                            corrections, s->g.n, B, s->k, s->d_lrp, s->d_lci, fail);

@@ -46,3 +46,27 @@ def test_lsd_mu_rounds_of_wide_shots():
     t = [_ms(lambda d=binding.Decoder(bc, code.priors, 8, max_iter=10, lsd_order=mu): d.lsd(s, llr)) for mu in (0, 1)]
     print(f"  LSD-0 {t[0]:.1f} ms, LSD-1 {t[1]:.1f} ms")
     assert t[1] <= 1.15 * t[0]
+
+
+def _flags(n, rows, weight, B):
+    """A call that scores B shots of n faults by logical rows of the given weight."""
+    rng = np.random.default_rng(1)
+    L = np.zeros((rows, n), dtype=np.uint8)
+    for q in range(rows):
+        L[q, rng.choice(n, size=weight, replace=False)] = 1
+    H = np.zeros((2, n), dtype=np.uint8)
+    H[0, ::2] = H[1, 1::2] = 1
+    smp = binding.Sampler(binding.Code.from_dense(H), np.full(n, 0.01), L if rows else None)
+    e, c = torch.zeros((2, B, n), dtype=torch.uint8, device="cuda")
+    f = torch.empty(B, dtype=torch.uint8, device="cuda")
+    return lambda: smp.failures_into(e, c, f)
+
+
+def test_failure_flags_by_logical_rows():
+    """6,000 shots of 8,800 faults: one row over half the faults costs what looking at every fault costs
+    (1.1 of it; 13 with one thread for the row), twelve rows of 14 a part of it (2,000 shots: 0.4; 1.0 if
+    every fault is read)."""
+    print("case cost failure flags", flush=True)
+    t = [_ms(_flags(8800, *a), passes=30) for a in ((0, 0, 6000), (1, 4400, 6000), (0, 0, 2000), (12, 14, 2000))]
+    print("  ms " + " ".join(f"{x:.4f}" for x in t))
+    assert t[1] <= 2.0 * t[0] and t[3] <= 0.7 * t[2]

@@ -63,3 +63,26 @@ def test_sampler(which, B, shift):
     Ht = torch.from_numpy(code.H).cuda().t().contiguous().float()
     for a in range(0, B, 8192):
         assert torch.equal(s[a:a + 8192], (c[a:a + 8192].float() @ Ht).remainder_(2).byte())
+
+
+# rows of logicals that one thread, several threads and several wavefronts share, and both kernels' sides of
+# the line between them
+@pytest.mark.parametrize("n,rows,weight,B", [(50, 1, 16, 70001), (50, 40, 17, 3), (50, 40, 17, 70000), (300, 3, 250, 40),
+                                             (300, 70, 33, 999), (2000, 1, 2000, 20000), (2000, 12, 14, 300),
+                                             (9001, 1, 4400, 33), (9001, 8, 880, 65), (9001, 2, 5, 3000)])
+def test_failures_by_rows(n, rows, weight, B):
+    print(f"case sampler_shapes rows {n} {rows} {weight} {B}", flush=True)
+    rng = np.random.default_rng(n + rows)
+    L = np.zeros((rows, n), dtype=np.uint8)
+    for q in range(rows):  # the last row is light, the one before it empty
+        L[q, rng.choice(n, size=weight if q < rows - 2 or rows < 3 else (0 if q == rows - 2 else 1), replace=False)] = 1
+    H = np.ones((1, n), dtype=np.uint8)
+    smp = binding.Sampler(binding.Code.from_dense(H), np.full(n, 0.01), L)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    e = (torch.rand((B, n), generator=gen, device="cuda") < 0.1).byte()
+    r = (torch.rand((B, n), generator=gen, device="cuda") < 2.0 / n).byte()
+    f = torch.empty(B, dtype=torch.uint8, device="cuda")
+    smp.failures_into(e, e ^ r, f)
+    Lt = torch.from_numpy(L).cuda().t().contiguous().float()
+    want = torch.cat([((r[a:a + 8192].float() @ Lt).remainder_(2) != 0).any(1) for a in range(0, B, 8192)])
+    assert torch.equal(f.bool(), want)
