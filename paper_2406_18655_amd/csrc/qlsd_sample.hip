@@ -215,7 +215,7 @@ __global__ void failure_kernel(const uint8_t *e, const uint8_t *c, int n, int B,
 }
 
 // For matrices whose bit-sliced shots do not fit in LDS (more than about 35,000 faults), and where they
-// are faster (failures_by_shot): a thread per (shot, detector), and a wavefront per shot.
+// are faster (syndromes_by_shot, failures_by_shot): a thread per (shot, detector), and a wavefront per shot.
 __global__ void syndrome_wide_kernel(const int32_t *row_ptr, const int32_t *col_idx, int m, int n, int B,
                                      const uint8_t *x, uint8_t *s) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -280,6 +280,14 @@ bool failures_by_shot(int n, int k, int64_t ones, int64_t steps, int B) {
     const double sliced = 4.0 + wide * std::min(B, 32) / 32.0 + (double)B * n / 2.8e6;
     return shot <= sliced;
 }
+
+// Whether syndrome_wide_kernel (a thread per detector of a shot) is the faster one: few shots in groups of
+// 32 leave most of the device idle.  Its time follows the entries of all shots' checks, and the longest
+// check where that is long; the sliced kernel's hardly changes.  Measured over 41 to 8,800 faults, both
+// in us beside a launch: 100 shots of 8,800 faults (26,672 entries) 9.9 against 17.6, 300 shots 21.6 / 18.7;
+// 300 shots of 1,600 (5,425 entries) 7.8 / 9.5, 1,000 shots 10.3 / 9.2; 1,000 shots of 900 (3,051 entries)
+// 7.7 / 8.0, 3,000 shots 13.6 / 8.4; checks of about 85 entries 18 / 15 at any number of shots.
+bool syndromes_by_shot(const DevGraph &g, int B) { return g.max_rw <= 48 && (int64_t)B * g.nnz < 3500000; }
 
 qlsd_status sfail(qlsd_status st, const char *fmt, ...) {
     va_list ap;
@@ -374,7 +382,7 @@ qlsd_status qlsd_syndromes(qlsd_sampler s, const uint8_t *x, int32_t B, uint8_t 
     if (B == 0) return QLSD_OK;
     const Slices k = slices_for(s->g.n, s->g.m, B);
     hipError_t e = hipSuccess;
-    if (k.words > 0) {
+    if (k.words > 0 && !syndromes_by_shot(s->g, B)) {
         e = hipFuncSetAttribute((const void *)syndrome_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
         if (e != hipSuccess) return sfail(QLSD_E_DEVICE, "syndrome launch: %s", hipGetErrorString(e));
         const int64_t shots = 32ll * k.words;

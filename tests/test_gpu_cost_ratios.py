@@ -70,3 +70,16 @@ def test_failure_flags_by_logical_rows():
     t = [_ms(_flags(8800, *a), passes=30) for a in ((0, 0, 6000), (1, 4400, 6000), (0, 0, 2000), (12, 14, 2000))]
     print("  ms " + " ".join(f"{x:.4f}" for x in t))
     assert t[1] <= 2.0 * t[0] and t[3] <= 0.7 * t[2]
+
+
+def test_syndromes_of_few_shots():
+    """32 shots of the detector error model take one group of bit-sliced shots: their syndromes cost what
+    one shot's flags cost, a launch (1.05 of it; 2.1 on one workgroup)."""
+    print("case cost few syndromes", flush=True)
+    code = synthetic_dem()
+    smp = binding.Sampler(binding.Code.from_dense(code.H), code.priors)
+    e = torch.zeros((32, code.n), dtype=torch.uint8, device="cuda")
+    s = torch.empty((32, code.m), dtype=torch.uint8, device="cuda")
+    t = [_ms(_flags(144, 1, 5, 1), passes=100), _ms(lambda: smp.syndromes_into(e, s), passes=100)]
+    print("  ms " + " ".join(f"{x:.4f}" for x in t))
+    assert t[1] <= 1.5 * t[0]

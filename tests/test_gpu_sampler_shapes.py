@@ -86,3 +86,23 @@ def test_failures_by_rows(n, rows, weight, B):
     Lt = torch.from_numpy(L).cuda().t().contiguous().float()
     want = torch.cat([((r[a:a + 8192].float() @ Lt).remainder_(2) != 0).any(1) for a in range(0, B, 8192)])
     assert torch.equal(f.bool(), want)
+
+
+# checks of up to 48 entries and of more, both kernels' sides of the line of 3.5 million entries, and shots that
+# are no whole groups or words
+@pytest.mark.parametrize("m,n,weight,B", [(20, 41, 4, 41666), (20, 41, 4, 42001), (33, 500, 48, 100), (33, 500, 49, 100),
+                                          (33, 500, 48, 2211), (936, 8800, 27, 31), (936, 8800, 27, 159)])
+def test_syndromes_by_entries(m, n, weight, B):
+    print(f"case sampler_shapes entries {m}x{n} weight {weight} {B}", flush=True)
+    rng = np.random.default_rng(m + n)
+    H = np.zeros((m, n), dtype=np.uint8)
+    for i in range(m):
+        H[i, rng.choice(n, size=weight, replace=False)] = 1
+    smp = binding.Sampler(binding.Code.from_dense(H), np.full(n, 0.01))
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = (torch.rand((B, n), generator=gen, device="cuda") < 0.1).byte()
+    s = torch.empty((B, m), dtype=torch.uint8, device="cuda")
+    smp.syndromes_into(x, s)
+    Ht = torch.from_numpy(H).cuda().t().contiguous().float()
+    for a in range(0, B, 8192):
+        assert torch.equal(s[a:a + 8192], (x[a:a + 8192].float() @ Ht).remainder_(2).byte())
