@@ -1,6 +1,6 @@
 // Learned reliability refinement between BP and LSD (include/qlsd_net.h): a 3-layer
 // message-passing network over the Tanner graph, hidden width 32.  Dense products run on
-// bf16 MFMA with float32 accumulation; neighbour means in float32.  Training: one workgroup of 16
+// bf16 MFMA with float32 accumulation; neighbour means in float32.  Training: one workgroup of 12
 // wavefronts per shot at a time, node features in LDS, and the gradient of every parameter in
 // registers across all shots a workgroup processes, added to the global gradient once per workgroup.
 #include <math.h>
@@ -69,15 +69,15 @@ struct NetArgs {
 };
 
 // Training: per-workgroup storage.  The shared part (bf16 weights, small vectors, u16 CSR/CSC tables)
-// always sits in LDS; net_shared_layout is also the measure of the graphs a net accepts.  The
-// activation part (the shot's inputs, features of every layer, aggregation and backward buffers) sits
-// in LDS after it when both fit, else in a workgroup-private slice of a device workspace (large
-// graphs such as the 936 x 8800 detector error model).
-__host__ __device__ inline size_t net_shared_layout(int n, int m, int E, bool train, size_t *o) {
+// always sits in LDS; net_shared_layout is also the measure of the graphs a net accepts (limit: with a
+// second copy of the vectors, which no kernel holds any more).  The activation part (the shot's inputs,
+// features of every layer, aggregation and backward buffers) sits in LDS after it when both fit, else in a
+// workgroup-private slice of a device workspace (large graphs such as the 936 x 8800 detector error model).
+__host__ __device__ inline size_t net_shared_layout(int n, int m, int E, bool limit, size_t *o) {
     size_t off = 0;
     o[0] = off; off += al16(sizeof(uint16_t) * 9 * 1024);
     o[1] = off; off += al16(sizeof(float) * SV_N);
-    o[2] = off; off += train ? al16(sizeof(float) * SV_N) : 0;
+    o[2] = off; off += limit ? al16(sizeof(float) * SV_N) : 0;
     o[3] = off; off += al16(sizeof(uint16_t) * ((size_t)m + 1 + E + n + 1 + E));
     o[4] = off; off += al16(sizeof(float) * 4);
     return off;
@@ -85,11 +85,11 @@ __host__ __device__ inline size_t net_shared_layout(int n, int m, int E, bool tr
 // Inputs (posteriors, tanh, scaled priors, true errors, reciprocal degrees of faults; syndrome signs,
 // reciprocal degrees of checks), features of every layer, the aggregation (one row per feature) and the
 // masked gradient (bf16), the gradients of
-// the fault features and of the products (float).
-__host__ __device__ inline size_t net_act_layout(int n, int m, size_t *o) {
+// the fault features and of the products (float).  tight: the scaled priors are read from memory.
+__host__ __device__ inline size_t net_act_layout(int n, int m, bool tight, size_t *o) {
     const int NP = pad16(n), MP = pad16(m), XP = NP > MP ? NP : MP;
     size_t off = 0;
-    o[0] = off; off += al16(sizeof(float) * (5 * (size_t)n + 2 * (size_t)m));
+    o[0] = off; off += al16(sizeof(float) * ((tight ? 4 : 5) * (size_t)n + 2 * (size_t)m));
     o[1] = off; off += al16(sizeof(uint16_t) * ((NL + 1) * (size_t)NP * HID + NL * (size_t)MP * HID));
     o[2] = off; off += al16(sizeof(uint16_t) * (size_t)(XP + 4) * HID);
     o[3] = off; off += al16(sizeof(uint16_t) * (size_t)XP * HID);
@@ -99,13 +99,18 @@ __host__ __device__ inline size_t net_act_layout(int n, int m, size_t *o) {
 constexpr int kTrainThreads = 768;
 constexpr int kTrainWaves = kTrainThreads / 64;
 constexpr int kTrainParts = 3;  // wavefronts that share a weight-gradient tile, each a third of the nodes
-// The transposed weights come after the shared part.  At the end they and the activations make room
-// for every wavefront's gradients: kTrainParts copies of the nine matrices, then per wavefront the small
-// vectors and the loss.
+// Where the activations lie.  kTrainLds: in LDS, after the shared part and the transposed weights.
+// kTrainTight: in LDS without transposed weights (operands gathered from the rows) and scaled priors, for
+// graphs just too large for kTrainLds: every graph of the decoder's row weights whose features, gradients
+// and tables fit in LDS trains there, so gradients on several streams do not meet in the net's workspace
+// and the first call allocates nothing.  kTrainWorkspace: in the workspace.  At the end the LDS after the
+// shared part makes room for every wavefront's gradients: kTrainParts copies of the matrices (kTrainTight:
+// of one layer's at a time), then per wavefront the small vectors and the loss.
+enum TrainPlace { kTrainWorkspace, kTrainTight, kTrainLds };
 constexpr size_t kNetTransposed = sizeof(uint16_t) * 9 * 1024;
-constexpr size_t kNetFlush = sizeof(float) * (kTrainParts * 9 * 1024 + kTrainWaves * (SV_N + 1));
-__host__ __device__ inline size_t net_lds_act(size_t act) {
-    return act + kNetTransposed > al16(kNetFlush) ? act : al16(kNetFlush) - kNetTransposed;
+__host__ __device__ constexpr int train_flush_layers(TrainPlace p) { return p == kTrainLds ? NL : 1; }
+constexpr size_t net_flush_bytes(TrainPlace p) {
+    return sizeof(float) * (kTrainParts * 3 * train_flush_layers(p) * 1024 + kTrainWaves * (SV_N + 1));
 }
 
 // Feature rows of 32 bf16: the 8-byte group q4 (4 features) of row v sits at position
@@ -124,13 +129,13 @@ __device__ __forceinline__ float4v unpack4(uint2 u) {
 __device__ __forceinline__ uint2 pack4(float4v v) { return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])); }
 
 // Forward and backward of one shot at a time on one workgroup of 12 wavefronts; LDSACT: the activations
-// sit in LDS.  Dense products are pairs of v_mfma_f32_16x16x16_bf16 (features 0..15, then 16..31),
+// sit in LDS (PLACE).  Dense products are pairs of v_mfma_f32_16x16x16_bf16 (features 0..15, then 16..31),
 // formed transposed (D = W X^T) so a lane receives four consecutive features of one node and stores
 // them as one word; a lane's operand, two groups of four features of one node, is gathered from the
 // node's neighbours, averaged in float32 and rounded to bf16 in registers (forward), or read as two
 // words.  Weight gradients sum over nodes: their operands are
 // columns of the feature rows, and the tiles (one of B or C and one of A per wavefront and layer, the
-// nodes split over two or four wavefronts) stay in registers across all shots of the workgroup.  The
+// nodes split over three wavefronts) stay in registers across all shots of the workgroup.  The
 // vectors' gradients stay in registers too: a thread always works on the same four features.
 //
 // A shot is bound by the latency of its phases (two per layer forward, four backward, of 1.6 to 4.4
@@ -143,24 +148,29 @@ __device__ __forceinline__ uint2 pack4(float4v v) { return make_uint2(pack_bf16x
 
 // DR, DC: every check has DR faults and every fault DC checks, so a node's neighbours are read
 // together; 0: the degrees come from the tables.
-template <bool LDSACT, int DR, int DC>
+template <TrainPlace PLACE, int DR, int DC>
 __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
+    constexpr bool LDSACT = PLACE != kTrainWorkspace, TIGHT = PLACE == kTrainTight, WCOL = PLACE == kTrainLds;
     extern __shared__ __align__(16) unsigned char smem[];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int n = A.g.n, m = A.g.m, E = A.g.nnz;
     const int NP = pad16(n), MP = pad16(m), XP = NP > MP ? NP : MP;
     size_t so[5], ao[5];
-    const size_t shared_bytes = net_shared_layout(n, m, E, true, so);
-    net_act_layout(n, m, ao);
+    const size_t shared_bytes = net_shared_layout(n, m, E, false, so);
+    net_act_layout(n, m, TIGHT, ao);
     unsigned char *wrow = smem + so[0];  // [layer][A,B,C][out] rows of 32 inputs, as feature rows
     float *sv = (float *)(smem + so[1]);
     uint16_t *rp = (uint16_t *)(smem + so[3]), *ci = rp + (m + 1), *cp = ci + E, *ri = cp + (n + 1);
     float *loss = (float *)(smem + so[4]);
-    unsigned char *wcol = smem + shared_bytes;  // LDSACT: [layer][A,B,C][in] rows of 32 outputs
+    unsigned char *wcol = smem + shared_bytes;  // WCOL: [layer][A,B,C][in] rows of 32 outputs
     unsigned char *act;
-    if constexpr (LDSACT) act = smem + shared_bytes + kNetTransposed;
+    if constexpr (LDSACT) act = smem + shared_bytes + (WCOL ? kNetTransposed : 0);
     else act = A.act + (size_t)blockIdx.x * A.act_stride;
-    float *Lsh = (float *)(act + ao[0]), *x0 = Lsh + n, *x1 = x0 + n, *ev = x1 + n, *rdf = ev + n, *sgn = rdf + n, *rdc = sgn + m;
+    float *Lsh = (float *)(act + ao[0]), *x0 = Lsh + n, *ev = x0 + n, *rdf = ev + n, *sgn = rdf + n, *rdc = sgn + m, *x1 = rdc + m;
+    auto scaled_prior = [&](int j) {
+        if constexpr (TIGHT) return A.lam[j] * 0.125f;
+        else return x1[j];
+    };
     auto Hrow = [&](int l) { return act + ao[1] + (size_t)l * NP * 64; };
     auto Crow = [&](int l) { return act + ao[1] + (size_t)(NL + 1) * NP * 64 + (size_t)(l - 1) * MP * 64; };
     unsigned char *AGG = act + ao[2], *DUV = act + ao[3], *DH = act + ao[4], *DT = DH + (size_t)NP * 128;
@@ -193,13 +203,14 @@ __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
     }
     for (int x = t; x <= m; x += kTrainThreads) rp[x] = (uint16_t)A.g.row_ptr[x];
     for (int x = t; x <= n; x += kTrainThreads) cp[x] = (uint16_t)A.g.col_ptr[x];
-    for (int j = t; j < n; j += kTrainThreads) x1[j] = A.lam[j] * 0.125f;
+    if constexpr (!TIGHT)
+        for (int j = t; j < n; j += kTrainThreads) x1[j] = A.lam[j] * 0.125f;
 #pragma unroll
     for (int k = 0; k < TH; k++) {
         const int x = t + k * kTrainThreads, mat = x >> 10, o = (x >> 5) & 31, i = x & 31;
         const uint16_t w = f2bf(th[k]);
         *(uint16_t *)(wrow + row2(mat * 32 + o, i)) = w;
-        if constexpr (LDSACT) *(uint16_t *)(wcol + row2(mat * 32 + i, o)) = w;
+        if constexpr (WCOL) *(uint16_t *)(wcol + row2(mat * 32 + i, o)) = w;
     }
     if (t < SV_N) sv[t] = svt;
     __syncthreads();
@@ -226,7 +237,7 @@ __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
     };
     // operand rows of W^T (inputs ct 16 .. + 15, k = outputs)
     auto wt_op = [&](int mat, int ct) -> Op {
-        if constexpr (LDSACT) {
+        if constexpr (WCOL) {
             return load_op(wcol, mat * 32 + ct * 16 + nl);
         } else {
             uint32_t h[8];
@@ -347,7 +358,7 @@ __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
             const int j = it >> 3;
             float4v h = zero4;
             if (j < n) {
-                const float a = x0[j], b = x1[j];
+                const float a = x0[j], b = scaled_prior(j);
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
                     const int f = q4 * 4 + u;
@@ -447,7 +458,7 @@ __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
                 if (l == 0) {
                     if (j < n) {
                         accx0 += dh * x0[j];
-                        accx1 += dh * x1[j];
+                        accx1 += dh * scaled_prior(j);
                         accb0 += dh;
                     }
                 } else {
@@ -511,13 +522,14 @@ __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
     // ---- flush: tiles (rows: out features, columns: in features), vectors, loss.  LDSACT: every
     // wavefront stores its own, then the workgroup adds the copies and adds the sums to the global
     // gradient (float atomics on LDS would take four cycles a lane: 43 us here).
-    float *parts = (float *)wcol, *vecs = parts + kTrainParts * 9 * 1024 + wave * (SV_N + 1);
+    constexpr int FL = train_flush_layers(PLACE), TILES = 3 * FL * 1024;  // layers, matrix entries at a time
+    float *parts = (float *)wcol, *vec0 = parts + kTrainParts * TILES, *vecs = vec0 + wave * (SV_N + 1);
     if constexpr (LDSACT) __syncthreads();
     auto add_tile = [&](int mat, float4v g) {
 #pragma unroll
         for (int u = 0; u < 4; u++) {
             const int at = (g_row + kq * 4 + u) * HID + g_col + nl;
-            if constexpr (LDSACT) parts[(g_part * 9 + mat) * 1024 + at] = g[u];
+            if constexpr (LDSACT) parts[g_part * TILES + (mat % (3 * FL)) * 1024 + at] = g[u];
             else atomicAdd(&A.grad[matrix_offset(mat) + at], g[u]);
         }
     };
@@ -525,12 +537,6 @@ __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
         if constexpr (LDSACT) vecs[x] = v;
         else atomicAdd(&A.grad[offset_of(x)], v);
     };
-#pragma unroll
-    for (int l = 0; l < NL; l++) {
-        add_tile(l * 3, ga[l]);
-        add_tile(l * 3 + 1, gb[l]);
-        add_tile(l * 3 + 2, gc[l]);
-    }
     // the vectors: the wavefront's eight threads of each feature group, then one lane per group
     auto flush4 = [&](int base, int stride, float4v v) {
 #pragma unroll
@@ -563,28 +569,39 @@ __global__ __launch_bounds__(kTrainThreads) void net_train_kernel(NetArgs A) {
         if constexpr (LDSACT) vecs[SV_N] = accloss;
         else atomicAdd(loss, accloss);
     }
-    __syncthreads();
-    if constexpr (LDSACT) {
-        // workgroups start at different places, so they do not queue on one address
-        constexpr int N = 9 * 1024 + SV_N + 1;
-        const int first = (int)((blockIdx.x * 64u * 37u) % (unsigned)N);
-        const float *vec0 = parts + kTrainParts * 9 * 1024;
-        for (int k = t; k < N; k += kTrainThreads) {
-            const int x = k + first < N ? k + first : k + first - N;
-            float s = 0.f;
-            if (x < 9 * 1024) {
 #pragma unroll
-                for (int c = 0; c < kTrainParts; c++) s += parts[c * 9 * 1024 + x];
-                atomicAdd(&A.grad[matrix_offset(x >> 10) + (x & 1023)], s);
-            } else {
-                const int y = x - 9 * 1024;
+    for (int l0 = 0; l0 < NL; l0 += FL) {
 #pragma unroll
-                for (int w = 0; w < kTrainWaves; w++) s += vec0[w * (SV_N + 1) + y];
-                atomicAdd(y < SV_N ? &A.grad[offset_of(y)] : A.loss, s);
-            }
+        for (int l = l0; l < l0 + FL; l++) {
+            add_tile(l * 3, ga[l]);
+            add_tile(l * 3 + 1, gb[l]);
+            add_tile(l * 3 + 2, gc[l]);
         }
-    } else if (t == 0) {
-        atomicAdd(A.loss, loss[0]);
+        if constexpr (LDSACT) {
+            __syncthreads();
+            // workgroups start at different places, so they do not queue on one address
+            const int N = TILES + (l0 == 0 ? SV_N + 1 : 0);
+            const int first = (int)((blockIdx.x * 64u * 37u) % (unsigned)N);
+            for (int k = t; k < N; k += kTrainThreads) {
+                const int x = k + first < N ? k + first : k + first - N;
+                float s = 0.f;
+                if (x < TILES) {
+#pragma unroll
+                    for (int c = 0; c < kTrainParts; c++) s += parts[c * TILES + x];
+                    atomicAdd(&A.grad[matrix_offset(3 * l0 + (x >> 10)) + (x & 1023)], s);
+                } else {
+                    const int y = x - TILES;
+#pragma unroll
+                    for (int w = 0; w < kTrainWaves; w++) s += vec0[w * (SV_N + 1) + y];
+                    atomicAdd(y < SV_N ? &A.grad[offset_of(y)] : A.loss, s);
+                }
+            }
+            if (l0 + FL < NL) __syncthreads();
+        }
+    }
+    if constexpr (!LDSACT) {
+        __syncthreads();
+        if (t == 0) atomicAdd(A.loss, loss[0]);
     }
 }
 
@@ -1170,22 +1187,28 @@ __global__ void adam_kernel(float *theta, const float *grad, float *m1, float *m
 
 }  // namespace
 
-static size_t net_shared_bytes(const DevGraph &g, bool train) {
+static size_t net_shared_bytes(const DevGraph &g, bool limit) {
     size_t o[5];
-    return net_shared_layout(g.n, g.m, g.nnz, train, o);
+    return net_shared_layout(g.n, g.m, g.nnz, limit, o);
 }
-static size_t net_act_bytes(const DevGraph &g) {
+static size_t net_act_bytes(const DevGraph &g, bool tight) {
     size_t o[5];
-    return net_act_layout(g.n, g.m, o);
+    return net_act_layout(g.n, g.m, tight, o);
 }
-// Training with the activations in LDS.
-static size_t net_train_lds(const DevGraph &g) {
-    return net_shared_bytes(g, true) + kNetTransposed + net_lds_act(net_act_bytes(g));
+static size_t net_train_lds(const DevGraph &g, TrainPlace p) {
+    const size_t shared = net_shared_bytes(g, false);
+    if (p == kTrainWorkspace) return shared;
+    const size_t act = net_act_bytes(g, p == kTrainTight) + (p == kTrainLds ? kNetTransposed : 0);
+    return shared + std::max(act, al16(net_flush_bytes(p)));
 }
-// ... which the kernel takes only where a thread covers each fault and each check of a shot, and a row's
-// offset fits 16 bits.
-static bool net_train_in_lds(const DevGraph &g) {
-    return net_train_lds(g) <= 159 * 1024 && std::max(pad16(g.n), pad16(g.m)) <= kTrainThreads;
+// Activations in LDS where a thread covers each fault and each check of a shot (a row's offset then fits 16
+// bits) and they fit.  1,000 shots of a code of
+// 176 faults and 88 checks: kTrainTight 131 us, in the workspace 761; of 150 and 75: kTrainLds 115, 750.
+static TrainPlace net_train_place(const DevGraph &g) {
+    if (std::max(pad16(g.n), pad16(g.m)) > kTrainThreads) return kTrainWorkspace;
+    for (TrainPlace p : {kTrainLds, kTrainTight})
+        if (net_train_lds(g, p) <= 159 * 1024) return p;
+    return kTrainWorkspace;
 }
 
 // Wavefronts per inference workgroup: 11 in one workgroup when they fit in a CU's 160 KB of LDS
@@ -1250,12 +1273,12 @@ static hipError_t launch_train(qlsd_net_s *net, NetArgs a, int grid, hipStream_t
         net->d_act = nullptr;
         return hipErrorOutOfMemory;
     }
-    size_t lds = net_train_lds(a.g);
-    if (net->d_act) {
+    const TrainPlace place = net_train_place(a.g);
+    const size_t lds = net_train_lds(a.g, place);
+    if (place == kTrainWorkspace) {
         a.act = net->d_act;
         a.act_stride = net->act_stride;
         grid = std::min(grid, net->act_slices);
-        lds = net_shared_bytes(a.g, true);
     }
     auto go = [&](auto kernel) {
         const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1263,10 +1286,11 @@ static hipError_t launch_train(qlsd_net_s *net, NetArgs a, int grid, hipStream_t
         hipLaunchKernelGGL(kernel, dim3(std::max(grid, 1)), dim3(kTrainThreads), lds, st, a);
         return hipGetLastError();
     };
-    if (net->d_act) return go(net_train_kernel<false, 0, 0>);
+    if (place == kTrainWorkspace) return go(net_train_kernel<kTrainWorkspace, 0, 0>);
+    if (place == kTrainTight) return go(net_train_kernel<kTrainTight, 0, 0>);
     const DevGraph &g = a.g;
     const bool reg63 = g.min_rw == 6 && g.max_rw == 6 && g.min_cw == 3 && g.max_cw == 3;
-    return reg63 ? go(net_train_kernel<true, 6, 3>) : go(net_train_kernel<true, 0, 0>);
+    return reg63 ? go(net_train_kernel<kTrainLds, 6, 3>) : go(net_train_kernel<kTrainLds, 0, 0>);
 }
 // Slices of the large-graph inference workspace: one per compute unit, so the grid's features
 // (about 0.7 MB per slice for the detector error model) stay in the last-level cache.
@@ -1346,8 +1370,8 @@ qlsd_status qlsd_net_create(qlsd_code code, const double *priors, const float *p
     net->num_cus = prop.multiProcessorCount;
     // wave-per-shot inference needs u16 byte offsets of feature rows (64 B each) and LDS room
     net->wave_infer = pad16(g.n) + 1 <= 1023 && pad16(g.m) + 1 <= 1023 && infer_lds_bytes(g) <= 160 * 1024;
-    if (!net_train_in_lds(g)) {  // training activations in a device workspace (allocated at first use)
-        net->act_stride = (net_act_bytes(g) + 255) & ~size_t(255);
+    if (net_train_place(g) == kTrainWorkspace) {  // training activations in a device workspace (allocated at first use)
+        net->act_stride = (net_act_bytes(g, false) + 255) & ~size_t(255);
         net->act_slices = net->num_cus;
     }
     if (!net->wave_infer) {

@@ -8,7 +8,7 @@ import pytest
 
 import oracle.learned as ol
 from paper_2406_18655_amd import binding
-from paper_2406_18655_amd.workloads import bivariate_bicycle, sample, surface_hgp
+from paper_2406_18655_amd.workloads import CheckMatrix, bivariate_bicycle, sample, surface_hgp
 from test_gpu_net import _theta
 
 pytestmark = pytest.mark.gpu
@@ -104,3 +104,51 @@ def test_gradient(which, B):
         worst = float((np.abs(a - b) / np.maximum(TOL * (np.abs(b) + np.sqrt(np.mean(b ** 2))), 1e-12)).max())
         assert worst <= 1.0, (name, worst)
         off += k
+
+
+def _random_code(n, m, weight, seed):
+    """m x n, columns of the given weight on the rows used least, no row above 32."""
+    rng = np.random.default_rng(seed)
+    H = np.zeros((m, n), dtype=np.uint8)
+    for j in range(n):
+        H[np.lexsort((rng.random(m), H.sum(1)))[:weight], j] = 1
+    assert H.sum(1).max() <= 32 and H.sum(1).min() >= 2
+    return CheckMatrix(name=f"{m}x{n}", H=H, priors=rng.uniform(0.02, 0.1, size=n),
+                       logicals=np.zeros((0, n), dtype=np.uint8))
+
+
+# around the line of features and transposed weights in LDS, and up to that of features alone
+CODES.update({"75x150": lambda: _random_code(150, 75, 3, 1), "100x150": lambda: _random_code(150, 100, 2, 2),
+              "16x208": lambda: _random_code(208, 16, 2, 3), "88x176": lambda: _random_code(176, 88, 3, 4)})
+
+
+@pytest.mark.parametrize("which,B", [("75x150", 1), ("75x150", 300), ("100x150", 3), ("16x208", 3), ("88x176", 3)])
+def test_gradient_without_a_workspace(which, B):
+    """Graphs whose features and gradients fit in LDS train there: right gradients, no allocation at the first
+    call, and calls on two streams that do not meet."""
+    code = CODES[which]()
+    e, S = sample(code, B, seed=62)
+    L = ((1 - 2.0 * e) * 3.0).astype(np.float32)
+    args = [torch.from_numpy(x).cuda() for x in (S, L, e)]
+    other = [x.flip(0).contiguous() if B > 1 else x ^ 1 if x.dtype == torch.uint8 else -x for x in args]
+    binding.Net(binding.Code.from_dense(CODES["surface3"]().H), CODES["surface3"]().priors, _theta(9))
+    net = binding.Net(binding.Code.from_dense(code.H), code.priors, _theta(9))
+    [torch.empty(binding.NET_PARAMS + 1, device="cuda") for _ in range(4)]  # the outputs' own memory
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    g0, l0 = net.gradient(*args)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 8 << 20
+    g1, _ = net.gradient(*other)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = []
+    for _ in range(3):
+        for st, a in zip(streams, (args, other)):
+            with torch.cuda.stream(st):
+                got.append(net.gradient(*a)[0])
+    torch.cuda.synchronize()
+    for k, g in enumerate(got):  # sums of the same terms in another order
+        want = (g0, g1)[k % 2]
+        assert (g - want).abs().max() <= 1e-4 * want.abs().max(), k
+    test_gradient(which, B)
