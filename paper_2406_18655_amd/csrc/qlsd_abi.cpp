@@ -362,13 +362,6 @@ static int bp_stride_for(qlsd_code c, int S, size_t budget, int threads) {
     return se;
 }
 
-// Threads of a slot-BP workgroup when wg of them share a CU: 16 wavefronts per CU in every shape (a
-// CU's one or two workgroups of larger graphs leave most of its issue slots empty at 256 threads).
-// BP 30 per launch, one workgroup of 256 / 512 / 1024 threads per CU: 432 x 900, 2,048 shots 0.485 /
-// 0.268 / 0.186 ms; 192 x 400, 8,192 shots 0.69 / 0.38 / 0.27; 768 x 1600, 2,048 shots 0.75 / 0.42 /
-// 0.29.  Two workgroups of 512 with half the slots each: 0.23, 0.27 and 0.39.
-static int bp_threads_for(int wg) { return wg >= 4 ? kBpThreads : wg >= 2 ? 2 * kBpThreads : kBpMaxThreads; }
-
 qlsd_status qlsd_decoder_create(qlsd_code code, const qlsd_params *params, const double *priors,
                                 int32_t max_batch, qlsd_decoder *out) {
     g_err[0] = 0;

@@ -13,6 +13,15 @@ namespace qlsd {
 constexpr int kBpThreads = 256;      // slot BP: four workgroups per CU
 constexpr int kBpMaxThreads = 1024;  // slot BP: one workgroup per CU
 
+// Threads of a slot-BP workgroup when wg of them share a CU.  The kernels are compiled for 16 wavefronts
+// per CU (four per SIMD), and the tiers that decoder creation uses, 1, 2 and 4, have just those (a CU's one
+// or two workgroups of larger graphs leave most of its issue slots empty at 256 threads); three have 12,
+// since of three workgroups of 8 only two could be resident, and more than four wait for room.
+// BP 30 per launch, one workgroup of 256 / 512 / 1024 threads per CU: 432 x 900, 2,048 shots 0.485 /
+// 0.268 / 0.186 ms; 192 x 400, 8,192 shots 0.69 / 0.38 / 0.27; 768 x 1600, 2,048 shots 0.75 / 0.42 /
+// 0.29.  Two workgroups of 512 with half the slots each: 0.23, 0.27 and 0.39.
+constexpr int bp_threads_for(int wg) { return wg >= 3 ? kBpThreads : wg == 2 ? 2 * kBpThreads : kBpMaxThreads; }
+
 // Device copy of H: CSR (checks -> faults) and CSC (faults -> checks); edge id = CSR position.
 struct DevGraph {
     int m, n, nnz;
