@@ -237,14 +237,6 @@ struct Basis<W, true, InLds> {
     }
 };
 
-template <int W>
-__device__ __forceinline__ int parity_and(const uint64_t (&a)[W], const uint64_t (&b)[W]) {
-    int c = 0;
-#pragma unroll
-    for (int w = 0; w < W; w++) c += __popcll(a[w] & b[w]);
-    return c & 1;
-}
-
 // parity of (row s of Mrow, or of CT) AND b over the slices in use (the first NS)
 template <int W, class BB, int NS = W>
 __device__ __forceinline__ int parity_M(const BB &B, int s, const uint64_t (&b)[W]) {
@@ -373,26 +365,23 @@ __device__ __forceinline__ void insert_apply(BB &B, const LsdLds &S, int col, in
     }
 }
 
-// The register basis reduces the column in the tier of the slices in use (a shot whose clusters
-// hold at most 64 rows costs a one-slice reduction); the device-memory basis tests each slice at
-// run time.
+// The register basis (the cluster-batched schedule's) reduces the column in the tier of the slices in use
+// (a shot whose clusters hold at most 64 rows costs a one-slice reduction); the device-memory basis tests
+// each slice at run time.
 template <int W, class BB>
 __device__ __forceinline__ bool insert_column(BB &B, const LsdLds &S, int col, int lane, int lr_src, int base, int cw) {
     InsertPlan<W> P;
     bool piv;
-    if constexpr (!BB::kInMem && W == 2) {
-        piv = B.ns <= 1 ? insert_plan<W, 1>(B, lane, lr_src, base, cw, P) : insert_plan<W, W>(B, lane, lr_src, base, cw, P);
-    } else if constexpr (!BB::kInMem && W == 4) {
+    if constexpr (!BB::kInMem) {
+        static_assert(W == 4, "the cluster-batched schedule's registers");
         piv = B.ns <= 1   ? insert_plan<W, 1>(B, lane, lr_src, base, cw, P)
               : B.ns <= 2 ? insert_plan<W, 2>(B, lane, lr_src, base, cw, P)
                           : insert_plan<W, W>(B, lane, lr_src, base, cw, P);
-    } else if constexpr (BB::kInMem && W >= 8) {
-        // memory bases: tiers of four slices (the loops still test each slice at run time)
+    } else {
+        // memory bases (W = 8, 16): tiers of four slices (the loops still test each slice at run time)
         if (B.ns <= 4) piv = insert_plan<W, 4>(B, lane, lr_src, base, cw, P);
         else if (W > 8 && B.ns <= 8) piv = insert_plan<W, (W > 8 ? 8 : W)>(B, lane, lr_src, base, cw, P);
         else piv = insert_plan<W, W>(B, lane, lr_src, base, cw, P);
-    } else {
-        piv = insert_plan<W, W>(B, lane, lr_src, base, cw, P);
     }
     if (!piv) return false;
     insert_apply<W>(B, S, col, lane, P);
