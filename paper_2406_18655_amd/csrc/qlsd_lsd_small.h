@@ -1,5 +1,5 @@
-// Per-shot LSD device code for small codes (one wavefront per shot): n <= 192 faults, m <= 128 checks,
-// columns of at most 6 checks, H in LDS.  The same function of a shot as decode_shot, with the clusters
+// Per-shot LSD device code for small codes (one wavefront per shot): n <= 192 faults, m <= 128 checks, H in
+// LDS, columns of any weight (lsd_small_shape).  The same function of a shot as decode_shot, with the clusters
 // held by the lanes instead of union-find arrays in LDS:
 //   * the shot's faults are ranked by key once, and sets of faults are bit sets over ranks (3 words);
 //   * lane c holds cluster c: its checks (a bit set), its candidates (the ranks of every fault that meets

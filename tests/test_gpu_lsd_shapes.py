@@ -208,3 +208,27 @@ def test_lsd_mu_after_a_frozen_cluster(oracle_mod, chain, copies, weight, mu):
         assert not inf["status"][b] & (binding.ST_OVERFLOW | binding.ST_BAD_LLR), b
         assert (c[b] == want).all(), b
         assert tuple(st[b]) == (stats[0], stats[1], stats[3], stats[6]), b
+
+
+# columns of up to 16 checks where the clusters are held by the lanes (at most 128 checks and 192 faults)
+@pytest.mark.parametrize("m,n,heavy", [(40, 100, 9), (64, 120, 16), (96, 190, 11), (128, 192, 16)])
+def test_lsd_of_small_heavy_graphs(oracle_mod, m, n, heavy):
+    print(f"case lsd_shapes small {m}x{n} weight {heavy}", flush=True)
+    H = _heavy_graph(m - 1, n, heavy - 2, seed=m + n + heavy)
+    H = np.vstack([H, H[:1]])  # a dependent check: syndromes outside the image
+    assert 1 <= H.sum(0).min() and 7 <= H.sum(0).max() <= 16 and H.sum(1).max() <= 32
+    S, L = _shots(H, seed=m * n, dense=8)
+    dec = binding.Decoder(binding.Code.from_dense(H), np.full(n, 0.02), len(S), max_iter=5)
+    corr, info, st = dec.lsd_stats(torch.from_numpy(S).cuda(), torch.from_numpy(L).cuda())
+    torch.cuda.synchronize()
+    c, st, inf = corr.cpu().numpy(), st.cpu().numpy(), binding.parse_info(info)
+    oc = oracle_mod.Code.from_dense(H)
+    unsat = 0
+    for b in range(len(S)):
+        want, ost, stats = oracle_mod.lsd(oc, S[b], L[b].astype(np.float64))
+        assert not inf["status"][b] & (binding.ST_OVERFLOW | binding.ST_BAD_LLR), b
+        assert (c[b] == want).all(), b
+        assert bool(inf["status"][b] & binding.ST_UNSAT) == bool(ost & oracle_mod.ST_UNSAT), b
+        assert tuple(st[b]) == (stats[0], stats[1], stats[3], stats[6]), b
+        unsat += bool(ost & oracle_mod.ST_UNSAT)
+    assert unsat
