@@ -971,6 +971,17 @@ __host__ __device__ inline size_t bp_graph3_state_offset(const DevGraph &g) {
     return align16(sizeof(float) * ((size_t)bp_graph3_words(g) + 1));
 }
 
+constexpr int kBpGraph3Degree = 7;  // largest column weight bp_graph3_kernel takes
+// Largest degree of the faults at positions 1024 k and up (LIM: of those past the first 1024).  The layout
+// spans less than 2^15 words and the 1024 k + 1 faults up to there have at least that degree, in groups of
+// 64 that take 64 words a degree.
+__host__ __device__ constexpr int bp_graph3_degree(int k, int LIM) {
+    if (k == 0) return kBpGraph3Degree;
+    if (LIM <= 4) return LIM;
+    const int most = 32767 / (1024 * k + 64);
+    return most < LIM ? most : LIM;
+}
+
 // Large graphs, check messages kept as check states.  The messages min-sum sends from one check take
 // two magnitudes and one sign product, so the check phase only writes a state per check -- the smallest
 // |q| and the second smallest, each with the sign product in its sign bit -- and the fault phase forms
@@ -986,22 +997,21 @@ __host__ __device__ inline size_t bp_graph3_state_offset(const DevGraph &g) {
 // base_g + 64 u + l); thread t takes the faults at positions t + k NT of the code's fault order and
 // the check at position t of its check order (both by decreasing weight), whose state is entry t.  A
 // group of 64 faults runs the code compiled for its largest degree (at most 7 for the first 1024
-// faults, LIM for the rest: the packed offsets are registers); a lighter fault's missing edges point
-// at state m, which is zero and adds +-0, and a lighter check's at a word of +inf, so no loop tests
-// a lane's own weight.  Same values as bp_graph_kernel: the same products, and sums in the same order
+// faults, LIM or less for the rest, bp_graph3_degree: the packed offsets are registers); a lighter
+// fault's missing edges point at state m, which is zero and adds +-0, and a lighter check's at a word
+// of +inf, so no loop tests a lane's own weight.  Same values as bp_graph_kernel: the same products, and sums in the same order
 // (the first fault phase, with no incoming messages, is q = lambda, below 2^64); minima and sign products
 // do not depend on the order a check visits its edges.
 //
-// BP 100 of 16,384 shots of the 936 x 8800 detector error model: 10.31 -> 5.51 ms (8.7 ms where LIM is 7
-// and the row's addresses spill), 37 shots at BP 30: 0.240 -> 0.130 ms.  Bound by VALU issue (busy 0.75
-// of CU cycles, LDS 0.60 with bank conflicts 0.19, before the clamps left the edges: about 446 VALU
+// BP 100 of 16,384 shots of the 936 x 8800 detector error model: 10.31 -> 5.51 ms, 37 shots at BP 30:
+// 0.240 -> 0.130 ms.  Bound by VALU issue (busy 0.75 of CU cycles, LDS 0.60 with bank conflicts 0.19, before the clamps left the edges: about 446 VALU
 // instructions per wavefront and iteration then, 400 now).  A fault order that halved the modelled
 // conflicts of the state reads changed nothing.
 template <int MAXRW, int FPT, int LIM>
 __global__ __launch_bounds__(kBpGraphThreads) void bp_graph3_kernel(BpArgs args) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int NT = kBpGraphThreads;
-    constexpr int CMAX = 7;
+    constexpr int CMAX = kBpGraph3Degree;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int m = args.g.m, n = args.g.n, MW = bp_graph3_words(args.g);
     float *msg = (float *)smem;                                         // MW words, then one of +inf
@@ -1018,7 +1028,7 @@ __global__ __launch_bounds__(kBpGraphThreads) void bp_graph3_kernel(BpArgs args)
     uint32_t chk[FPT][(CMAX + 1) / 2];  // byte offsets of the states of the fault's checks, two u16
 #pragma unroll
     for (int k = 0; k < FPT; k++) {
-        const int lim = k == 0 ? CMAX : LIM;
+        const int lim = bp_graph3_degree(k, LIM);
         const int p = t + k * NT;
         int cw = 0, c0 = 0, b = 0;
         lam[k] = 0.f;
@@ -1128,7 +1138,7 @@ __global__ __launch_bounds__(kBpGraphThreads) void bp_graph3_kernel(BpArgs args)
 #pragma unroll
             for (int k = 0; k < FPT; k++)
 #pragma unroll
-                for (int u = 0; u < (k == 0 ? CMAX : LIM); u += 2) asm volatile("" : "+v"(chk[k][u / 2]));
+                for (int u = 0; u < bp_graph3_degree(k, LIM); u += 2) asm volatile("" : "+v"(chk[k][u / 2]));
             auto fault = [&](auto Dc, int k) -> float {
 #pragma clang fp contract(off)  // the products round before the sums, as in bp_graph_kernel
                 constexpr int D = decltype(Dc)::value;
@@ -1180,11 +1190,11 @@ __global__ __launch_bounds__(kBpGraphThreads) void bp_graph3_kernel(BpArgs args)
                     case 2: L[k] = fault(std::integral_constant<int, 2>{}, k); break;
                     case 3: L[k] = fault(std::integral_constant<int, 3>{}, k); break;
                     case 4: L[k] = fault(std::integral_constant<int, 4>{}, k); break;
-                    default:
+                    default:  // (which slots may hold the degree is known when the loop is unrolled)
                         if constexpr (LIM > 4) {
-                            if (grp[k] >> 16 == 5) L[k] = fault(std::integral_constant<int, 5>{}, k);
-                            else if (grp[k] >> 16 == 6) L[k] = fault(std::integral_constant<int, 6>{}, k);
-                            else L[k] = fault(std::integral_constant<int, CMAX>{}, k);
+                            if (bp_graph3_degree(k, LIM) >= 5 && grp[k] >> 16 == 5) L[k] = fault(std::integral_constant<int, 5>{}, k);
+                            else if (bp_graph3_degree(k, LIM) >= 6 && grp[k] >> 16 == 6) L[k] = fault(std::integral_constant<int, 6>{}, k);
+                            else if (bp_graph3_degree(k, LIM) >= 7) L[k] = fault(std::integral_constant<int, CMAX>{}, k);
                         } else if (k == 0) {
                             if (grp[k] >> 16 == 5) L[k] = fault(std::integral_constant<int, 5>{}, 0);
                             else if (grp[k] >> 16 == 6) L[k] = fault(std::integral_constant<int, 6>{}, 0);
@@ -1381,10 +1391,14 @@ hipError_t launch_bp_graph(const BpArgs &a, int grid, hipStream_t st) {
     const DevGraph &g = a.g;
     if (g.m <= kBpGraphThreads && g.max_rw <= 32 && g.max_cw <= 7 && g.n <= 9 * kBpGraphThreads && g.fault_order &&
         g.check_order && g.fault_msg && g.row_msg && g.msg_words > 0 && g.msg_words < 32768) {
-        // offsets of up to four checks for the faults past the first 1024 fit in registers; of up to
-        // seven they do not quite (the row's addresses are then re-read from scratch: 8.7 against
-        // 5.5 ms on the detector error model, still ahead of the 10.3 ms of messages rewritten in LDS)
-        return g.deep_cw <= 4 ? launch_bp_graph3_t<32, 9, 4>(a, grid, st) : launch_bp_graph3_t<32, 9, 7>(a, grid, st);
+        // The offsets of up to four checks of the faults past the first 1024 fit in registers with everything
+        // else; of more they fit for seven slots of faults (but for 2 or 16 words of 64 faults), not quite
+        // for nine (27).  BP 100 of 4,000 shots: 1000 x 7000, columns of 2 to 5, <7, 6> 5.45 ms, <7, 7> 5.88,
+        // nine slots of seven 10.2; 1000 x 7100, up to 7, <7, 7> 6.51 ms; 1000 x 9200, up to 7, <9, 7>
+        // 7.65, 21.1 when every slot held seven (11.4, 12.0 and 13.4 ms with messages rewritten in LDS).
+        if (g.deep_cw <= 4) return launch_bp_graph3_t<32, 9, 4>(a, grid, st);
+        if (g.n > 7 * kBpGraphThreads) return launch_bp_graph3_t<32, 9, 7>(a, grid, st);
+        return g.deep_cw <= 6 ? launch_bp_graph3_t<32, 7, 6>(a, grid, st) : launch_bp_graph3_t<32, 7, 7>(a, grid, st);
     }
     if (a.g.max_rw <= 8 && a.g.max_cw <= 4) return launch_bp_graph_t<8, 4>(a, grid, lds, st);
     if (a.g.max_rw <= 16 && a.g.max_cw <= 8) return launch_bp_graph_t<16, 8>(a, grid, lds, st);

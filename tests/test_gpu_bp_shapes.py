@@ -125,3 +125,33 @@ def test_large_graph_posteriors(oracle_mod, which, flags):
     for b in range(5):
         _r24.check_shot(oracle_mod, oc, lam, S[b], T, L32[b], inf["status"][b] & 1, inf["bp_iters"][b],
                         early_exit=flags == 0, hard32=h32[b])
+
+
+# as many heavy columns as a layout below 2^15 words holds: the last of weight 7 past position 4096, of 6 past
+# 5120, of 5 past 6144 and of 4 past 7168 (each with and without faults past 7 x 1024)
+@pytest.mark.parametrize("weight,heavy,n", [(7, 4097, 7650), (7, 4097, 7000), (6, 5121, 6700), (5, 6145, 7750),
+                                            (5, 6145, 7168), (4, 7169, 9216), (7, 1025, 9216)])
+def test_large_graph_of_heavy_columns(oracle_mod, weight, heavy, n):
+    print(f"case bp_shapes large {heavy} of weight {weight} among {n}", flush=True)
+    m = 1024
+    rng = np.random.default_rng(n + weight)
+    H = np.zeros((m, n), dtype=np.uint8)
+    load = np.zeros(m)
+    at = rng.permutation(n)
+    for k, j in enumerate(at):
+        rows = np.argsort(load + rng.random(m))[:weight if k < heavy else 1]
+        H[rows, j] = 1
+        load[rows] += 1
+    assert 2 <= load.min() and load.max() <= 32
+    assert -(-heavy // 64) * weight + -(-(n - heavy) // 64) < 512  # words of the layout / 64
+    priors = rng.uniform(0.001, 0.05, size=n)
+    e = (rng.random((4, n)) < priors / 4).astype(np.uint8)
+    S = ((e.astype(np.int64) @ H.T.astype(np.int64)) & 1).astype(np.uint8)
+    dec = binding.Decoder(binding.Code.from_dense(H), priors, 4, max_iter=12)
+    llr, hard, info = dec.bp(torch.from_numpy(S).cuda())
+    torch.cuda.synchronize()
+    L32, h32, inf = llr.cpu().numpy(), hard.cpu().numpy(), binding.parse_info(info)
+    oc = oracle_mod.Code.from_dense(H)
+    lam = oracle_mod.llr_from_priors(priors)
+    for b in range(4):
+        _r24.check_shot(oracle_mod, oc, lam, S[b], 12, L32[b], inf["status"][b] & 1, inf["bp_iters"][b], hard32=h32[b])
