@@ -334,7 +334,7 @@ qlsd_status qlsd_sampler_create(qlsd_code code, const double *priors, int32_t k,
     // is exact, is below 2^53
     uint64_t *thr = new (std::nothrow) uint64_t[g.n];
     hipError_t e = thr ? hipMalloc((void **)&s->d_thr, sizeof(uint64_t) * g.n) : hipErrorOutOfMemory;
-    for (int j = 0; thr && j < g.n; j++) thr[j] = (uint64_t)ceil(ldexp(priors[j], 53)) << 11;
+    for (int j = 0; thr && j < g.n; j++) thr[j] = (uint64_t)ceil(priors[j] * 0x1p53) << 11;
     if (e == hipSuccess) e = hipMemcpy(s->d_thr, thr, sizeof(uint64_t) * g.n, hipMemcpyHostToDevice);
     delete[] thr;
     if (e == hipSuccess) e = hipMalloc((void **)&s->d_lrp, sizeof(int) * (k + 1));
