@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2406_18655_amd import binding
-from paper_2406_18655_amd.workloads import synthetic_dem
+from paper_2406_18655_amd.workloads import bivariate_bicycle, sample, synthetic_dem
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -103,3 +103,16 @@ def test_bp_of_heavy_columns():
         t.append(_ms(lambda: dec.bp(s), passes=3))
     print("  ms " + " ".join(f"{x:.4f}" for x in t))
     assert t[0] <= 2.0 * t[1]
+
+
+def test_decode_of_easy_batches():
+    """1,500 shots that BP solves at once: a decode is BP, the end of its kernel and two short launches, 1.5
+    times BP as a kernel of its own (2.3 where a thousand wavefronts poll for LSD work that never comes)."""
+    print("case cost easy batch", flush=True)
+    code = bivariate_bicycle(p=0.003)
+    s = torch.from_numpy(sample(code, 1500, seed=5)[1]).cuda()
+    dec = binding.Decoder(binding.Code.from_dense(code.H), code.priors, 1500, max_iter=30)
+    corr = torch.empty((1500, code.n), dtype=torch.uint8, device="cuda")
+    t = [_ms(lambda: dec.bp(s), passes=50), _ms(lambda: dec.decode_into(s, corr), passes=50)]
+    print("  ms " + " ".join(f"{x:.4f}" for x in t))
+    assert t[1] <= 2.0 * t[0]
