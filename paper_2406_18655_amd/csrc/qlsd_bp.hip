@@ -228,8 +228,7 @@ struct CheckItem {
 // Control words (L.ctl), written by slot management for every wavefront: [0] retired, [1] fresh,
 // [2] active this iteration; [3] retired without converging; [5] request pending; [6] load scheduled (base, -1 none), [7] its
 // count, [8] its buffer.  Before the loop: [9] queue exhausted, [10] / [11] base (-1: none) and
-// count of the first chunk.  Fused: [12] shots this workgroup has published, [13] length of the published
-// list after the last of them.
+// count of the first chunk.  Fused: [12] shots this workgroup has published.
 // Hand-over between workgroups in the fused kernel.  The L2 caches of different XCDs are not
 // coherent with each other, so every word that crosses workgroups during the kernel -- the LLR
 // row of an unsolved shot, its list entry, the counters -- is written and read only with
@@ -361,7 +360,7 @@ void bp_lds_kernel(BpArgs args, FuseArgs f) {
         L.ctl[9] = b0 + C >= args.B;
         L.ctl[10] = c0 > 0 ? b0 : -1;
         L.ctl[11] = c0;
-        L.ctl[12] = L.ctl[13] = 0;
+        L.ctl[12] = 0;
     }
     __syncthreads();
     if (L.ctl[10] >= 0) {
@@ -653,7 +652,6 @@ void bp_lds_kernel(BpArgs args, FuseArgs f) {
                 if (t == 64) {
                     int pos = atomicAdd(f.tail, nunsolved);
                     L.ctl[12] += nunsolved;
-                    L.ctl[13] = pos + nunsolved;
                     for (int r = 0; r < nret; r++)
                         if (!L.rconv[r]) atomicExch(f.list_w + pos++, L.rshot[r]);
                 }
@@ -699,14 +697,13 @@ void bp_lds_kernel(BpArgs args, FuseArgs f) {
         // ---- LSD on published shots: the slot arrays are dead, the graph tables stay
         __syncthreads();
         if (t == 0) atomicAdd(f.bp_done, 1);  // after this workgroup's last reservation
-        // Where few of the batch are left to LSD (less than 1 in 32, as far as this workgroup has seen), one of
-        // its wavefronts waits for work and as many more go on as it has published shots: a wavefront without
-        // work polls atomics on the same three words as all others, one after the other.  [[144,12,12]] at
-        // 0.3%, all shots solved by BP: 256 shots 42.5 -> 26.8 us, 8,000 shots 91 -> 49.  (At 6%, 40% left to
-        // LSD, so few wavefronts would make 20,000 shots 3.5% slower.)
-        const int mine = L.ctl[12], seen = L.ctl[13];
-        __syncthreads();  // (the words lie where LSD's arrays go)
-        if (wave >= f.lsd_waves || (wave > mine && (long long)seen * 32 < args.B)) return;
+        // One of its wavefronts waits for LSD work, and as many more go on as it has published shots: a
+        // wavefront without work polls atomics on the same three words as all others, one after the other.
+        // [[144,12,12]] at 0.3%, all shots solved by BP: 256 shots 42.5 -> 26.8 us, 8,000 shots 91 -> 49; at
+        // 5%, 8,000 shots 202 -> 186.
+        const int published = L.ctl[12];
+        __syncthreads();  // (the word lies where LSD's arrays go)
+        if (wave >= f.lsd_waves || wave > published) return;
         __builtin_amdgcn_s_setprio(0);
         constexpr int K = 64 * LSDW;
         unsigned char *lbase = smem + tables_bytes(m, n, E, REG) + (size_t)wave * f.lsd.wave_bytes;
