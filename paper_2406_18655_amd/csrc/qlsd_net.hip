@@ -1202,8 +1202,8 @@ static size_t net_train_lds(const DevGraph &g, TrainPlace p) {
     return shared + std::max(act, al16(net_flush_bytes(p)));
 }
 // Activations in LDS where a thread covers each fault and each check of a shot (a row's offset then fits 16
-// bits) and they fit.  1,000 shots of a code of
-// 176 faults and 88 checks: kTrainTight 131 us, in the workspace 761; of 150 and 75: kTrainLds 115, 750.
+// bits) and they fit.  1,000 shots of a code of 176 faults and 88 checks: kTrainTight 131 us, in the workspace
+// 761; of 150 faults and 75 checks: kTrainLds 115, in the workspace 750.
 static TrainPlace net_train_place(const DevGraph &g) {
     if (std::max(pad16(g.n), pad16(g.m)) > kTrainThreads) return kTrainWorkspace;
     for (TrainPlace p : {kTrainLds, kTrainTight})
